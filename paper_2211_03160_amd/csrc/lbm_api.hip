@@ -199,6 +199,7 @@ struct lbm_ctx {
     int cond_axis;
     bool view;    // a cavity owned by a batch: the batch steps and initialises it
     int32_t steps_per_launch;  // time steps per launch of lbm_step (1-5 in 2D, 1-2 in 3D)
+    bool steps_set;            // the count was set by the caller: launches take exactly it
     int cus;                   // compute units of the device
     bool poison;               // debug: fill the destination state with NaN before every launch
     char err[512];
@@ -630,6 +631,89 @@ template <class St, int NS, int D> void stream_launches(lbm_ctx* c, int64_t k) {
     }
 }
 
+// k launches of the LDS tile kernel of `steps` steps each, A -> B
+template <class St, int RX, int RY, int KT> void tile2_launches(lbm_ctx* c, int64_t k, int steps) {
+    const uint32_t ox = RX - 2 * (steps - 1), oy = RY - 2 * (steps - 1);
+    Tile2Args<St> a{};
+    a.geo = c->geo;
+    a.c = make_coef<typename St::R>(c);
+    a.steps = steps;
+    a.tiles_x = (c->geo.nx + ox - 1) / ox;
+    a.tiles = a.tiles_x * ((c->geo.ny + oy - 1) / oy);
+    a.blocks_per_xcd = (a.tiles + kXcd - 1) / kXcd;
+    a.flux = c->flux(0, 0);
+    a.slot[0] = 0;
+    a.slot[1] = (uint32_t)c->lay.flux_doubles;
+    const dim3 grid(a.blocks_per_xcd * kXcd), block(RX * RY);
+    for (int64_t s = 0; s < k; ++s) {
+        const auto A = pops<St>(c, c->cur), B = pops<St>(c, 1 - c->cur);
+        a.fsrc = A.f;
+        a.gsrc = A.g;
+        a.fdst = B.f;
+        a.gdst = B.g;
+        a.t_parity = (int32_t)(c->t & 1);
+        poison_dst(c);
+        hipLaunchKernelGGL((tile2_kernel<St, RX, RY, KT>), grid, block, 0, c->stream, a);
+        c->cur = 1 - c->cur;
+        c->t += steps;
+    }
+}
+
+// n steps with the tile kernel: launches of K steps on RX x RY regions (KT:
+// K compiled in, or 0), the rest in one launch of fewer steps.  Leaves one
+// step over (returned) when the rest is one: the one-step kernel's.
+template <class St, int RX, int RY, int KT> int64_t tile2_run(lbm_ctx* c, int64_t n, int K) {
+    if (n >= K) tile2_launches<St, RX, RY, KT>(c, n / K, K);
+    const int rest = (int)(n % K);
+    if (rest >= 2) tile2_launches<St, 16, 16, 0>(c, 1, rest);
+    return rest == 1 ? 1 : 0;
+}
+
+// Largest grid the tile kernel steps by default.  Measured on square
+// cavities, us per step, tile / streaming kernel (its best segment length):
+// FP32 2049x1537 24.7 / 30.3, 3073^2 71.6 / 69.6, 4097^2 124.8 / 113.3; FP16
+// 22.1 / 28.3, 67.6 / 68.3, 119 / 112; BF16 20.4 / 30.5, 61.8 / 70.0, 108 /
+// 112, 8193^2 437 / 364; FP16-f+FP32-g 21.9 / 31.9, 69.7 / 74.1, 121 / 120.
+// FP64 8193^2 1096 / 1779: the streaming kernel holds two steps at most.
+template <class St> constexpr uint32_t tile2_most_nodes() {
+    if (sizeof(typename St::R) == 8) return UINT32_MAX;
+    constexpr bool same = sizeof(typename St::TF) == sizeof(typename St::TG);
+    constexpr bool bf16 = std::is_same_v<typename St::EF, EB16>;
+    return bf16 || !same ? 15000000u : 9000000u;
+}
+
+// n steps of a 2D cavity whose steps per launch were not set: through the
+// tile kernel where it is the fastest; returns the steps left over.
+//
+// The region grows with the grid, which trades the latency of a launch (K
+// collisions of one wavefront per SIMD in a 16 x 16 region) for less halo
+// recompute: 16 x 16 up to two tiles per compute unit, 32 x 16 up to four,
+// then 32 x 32.  us per step in FP32 with the three regions: 65^2 1.25 / 1.28
+// / 1.68 (the one-step kernel 3.2, the streaming kernel 17.4), 129^2 1.29 /
+// 1.30 / 1.74, 257^2 1.81 / 1.63 / 1.80, 513^2 4.36 / 3.19 / 2.80, 1025^2 15.2
+// / 10.0 / 8.6 (streaming 17.8).  FP64 keeps 32 x 16 with four steps (1025^2
+// 17.1 against 18.0 with 32 x 32; streaming 41.7): its 64-bit LDS planes of
+// a 32 x 32 region would leave one block per compute unit.  16-bit storage
+// runs four steps on 32 x 32 regions (FP16 2049x1537 22.1 against 23.6 with
+// five): each step spends 30 % of its instructions on the rounding.  Grids
+// lower than a tile's 24 output rows keep the streaming kernel, whose
+// segments fit any height, unless the launch is latency-bound anyway.
+template <class St> int64_t tile2_auto(lbm_ctx* c, int64_t n) {
+    const uint32_t nx = c->geo.nx, ny = c->geo.ny;
+    if (c->geo.N > tile2_most_nodes<St>() || (ny < 24 && c->geo.N > 65536u)) return n;
+    constexpr bool f64 = sizeof(typename St::R) == 8;
+    constexpr int kMid = f64 ? 4 : 5, kBig = sizeof(typename St::TF) == 4 ? 5 : 4;
+    auto tiles = [&](uint32_t ox, uint32_t oy) { return (uint64_t)((nx + ox - 1) / ox) * ((ny + oy - 1) / oy); };
+    const uint64_t cus = (uint64_t)std::max(c->cus, 1);
+    if (tiles(8, 8) <= 2 * cus) return tile2_run<St, 16, 16, 0>(c, n, 5);
+    if constexpr (f64) {
+        return tile2_run<St, 32, 16, kMid>(c, n, kMid);
+    } else {
+        if (tiles(24, 8) <= 4 * cus) return tile2_run<St, 32, 16, kMid>(c, n, kMid);
+        return tile2_run<St, 32, 32, kBig>(c, n, kBig);
+    }
+}
+
 // z segments of the 3D two-step kernel.  Each segment repeats the first
 // step on one plane below and one above it, and its block holds a compute
 // unit's LDS for the whole segment, so a launch runs in rounds: each XCD
@@ -751,6 +835,7 @@ lbm_status create_ctx(const lbm_params* p, void* d_workspace, size_t bytes, void
     c->cur = 0;
     c->t = -1;
     c->steps_per_launch = view ? 1 : default_steps_per_launch(p->dim, p->storage);
+    c->steps_set = false;
     Geometry& g = c->geo;
     g.nx = p->n[0];
     g.ny = p->n[1];
@@ -865,6 +950,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
         using St = decltype(stc);
         if constexpr (DIM == 2) {
             constexpr bool deep = sizeof(typename St::R) == 4;  // FP64: at most two (kMaxStepsFp64)
+            if (!c->steps_set) n = tile2_auto<St>(c, n);
             const int32_t spl = streamable(c) ? c->steps_per_launch : 1;
             if constexpr (five_steps<St>()) {
                 if (spl == 5 && n >= 5) {
@@ -931,6 +1017,7 @@ lbm_status lbm_set_steps_per_launch(lbm_ctx* c, int32_t steps) {
     if (steps == 5 && c->p.storage != LBM_FP32)
         return set_err(c->err, LBM_E_UNSUPPORTED, "five steps per launch need FP32 storage");
     c->steps_per_launch = steps;
+    c->steps_set = true;
     return LBM_OK;
 }
 

@@ -302,7 +302,9 @@ class Cavity:
     @property
     def steps_per_launch(self) -> int:
         """Steps per kernel launch of step(): 1 .. 5 in 2D, 1 or 2 in 3D; a
-        cavity starts with the fastest count for its storage mode."""
+        cavity starts with the fastest count for its storage mode on a large
+        grid, and until a count is set step() takes the launches that are
+        fastest for the grid's size (lbm.h)."""
         return int(lib().lbm_get_steps_per_launch(self._h))
 
     @steps_per_launch.setter
