@@ -39,6 +39,43 @@ unsigned grid1(size_t n, unsigned bs = 256, unsigned cap = 65536) {
 
 bool pos(int32_t v) { return v > 0; }
 
+constexpr size_t kMaxLds = 160 * 1024;
+
+template <int WM, int WN, int MT, int NT> bool conv3x3_lds_go(ConvArgs a, uint32_t taps, hipStream_t s) {
+    constexpr uint32_t BM = 16 * MT * WM, BN = 16 * NT * WN;
+    a.tap_group = taps;
+    const size_t lds = conv_lds_bytes(BM, BN, taps, (uint32_t)a.cin);
+    const uint64_t blocks = ((uint64_t)a.P + BM - 1) / BM * ((uint32_t)a.cout / BN);
+    if (lds > kMaxLds || blocks > 0x7ffffff0ull) return false;
+    hipLaunchKernelGGL((conv3x3_lds_kernel<WM, WN, MT, NT>), dim3((unsigned)((blocks + 7) / 8 * 8)),
+                       dim3(64 * WM * WN), lds, s, a);
+    return true;
+}
+
+// The LDS convolution where it applies: whole K steps inside a tap (cin a
+// multiple of 32) and operands that fit the LDS.  The block follows the
+// shape; us for pixels x channels (wavefronts, tiles per wavefront):
+//   32 input channels: the stages are short, so each takes 256 pixels: 32 ->
+//     96 at 16 x 136 x 136 41 with 256 x 32, 52 with 128 x 32;
+//   up to 96: 128 x 32, the weights of three taps per stage: 64 -> 64 at 68 x
+//     68 15.4 against 16.9 (256 x 32) and 17.7 (one tap per stage);
+//   more: 64 x 64, one tap per stage: 128 -> 128 at 34 x 34 16.5 against 18.8
+//     (128 x 32); 192 -> 64 at 68 x 68 42 / 45;
+//   fewer than two such blocks per compute unit: 64 x 32: 256 -> 256 at 17 x
+//     17 19.7 against 22.3;
+//   cout not a multiple of 32: 256 x 16 (32 -> 16 at 136 x 136: 14.3, and
+//     23.0 with conv3x3_kernel).
+bool conv3x3_lds(const ConvArgs& a, hipStream_t s) {
+    if (a.cin % 32 || 18.0 * a.cin * a.cout > 4.0e9) return false;
+    const uint32_t taps = a.cin <= 96 ? 3 : 1;
+    if (a.cout % 32) return conv3x3_lds_go<4, 1, 4, 1>(a, taps, s) || conv3x3_lds_go<4, 1, 1, 1>(a, 1, s);
+    const uint64_t few = 512, wide = ((uint64_t)a.P + 255) / 256 * ((uint32_t)a.cout / 32);
+    if (a.cin == 32 && wide >= few && conv3x3_lds_go<4, 1, 4, 2>(a, taps, s)) return true;
+    if (a.cin <= 96 && 2 * wide >= few && conv3x3_lds_go<4, 1, 2, 2>(a, taps, s)) return true;
+    if (a.cout % 64 == 0 && 2 * wide >= few && conv3x3_lds_go<2, 2, 2, 2>(a, taps, s)) return true;
+    return conv3x3_lds_go<2, 2, 2, 1>(a, taps, s);
+}
+
 }  // namespace
 
 extern "C" {
@@ -52,7 +89,8 @@ lbm_status lbm_nn_conv3x3(const uint16_t* x, int32_t n, int32_t h, int32_t w, in
         return nn_fail(LBM_E_INVALID, "conv3x3: bad shape n=%d h=%d w=%d cin=%d cout=%d", n, h, w, cin, cout);
     const double P = (double)n * h * w;
     if (P * (cin > cout ? cin : cout) > 4.0e9) return nn_fail(LBM_E_INVALID, "conv3x3: tensor too large");
-    ConvArgs a{x, wt, bias, y, n, h, w, cin, cout, relu, (uint32_t)P, (uint32_t)((P + 15) / 16)};
+    ConvArgs a{x, wt, bias, y, n, h, w, cin, cout, relu, (uint32_t)P, (uint32_t)((P + 15) / 16), 0};
+    if (conv3x3_lds(a, (hipStream_t)stream)) return launched("conv3x3");
     const int NT = cout % 64 == 0 ? 4 : cout % 32 == 0 ? 2 : 1;
     // pixel tiles per wavefront: as many as keep at least 4096 wavefronts
     // (16 per compute unit) in the launch

@@ -38,6 +38,14 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);  // nearest even
 }
 
+// 16 bytes at a buffer's byte offset (a lane's part plus a uniform one); zeros past its end
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t nn_rsrc(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ v4u nn_load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_offset, uint32_t offset) {
+    return __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_offset, (int)offset, 0));
+}
+
 struct ConvArgs {
     const uint16_t* x;   // [P][cin], P = n h w
     const uint16_t* wt;  // [9][cout][cin]
@@ -45,6 +53,7 @@ struct ConvArgs {
     uint16_t* y;         // [P][cout]
     int32_t n, h, w, cin, cout, relu;
     uint32_t P, ptiles;  // pixels, 16-pixel tiles
+    uint32_t tap_group;  // conv3x3_lds_kernel: taps whose weights are staged together (1 or 3)
 };
 
 // One wavefront computes 16 MT pixels x (16 NT) output channels: each K
@@ -114,6 +123,213 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(ConvArgs a) {
                     a.y[(size_t)q * a.cout + co] = f2bf(v);
                 }
             }
+    }
+}
+
+// The same convolution with both operands staged in LDS, for cin a multiple
+// of 32.  A block of WM x WN wavefronts computes 16 MT WM consecutive pixels
+// x 16 NT WN output channels.  Per tap row dy it stages the source pixels
+// p + dy w - 1 .. p + dy w + 1 of its pixels p (all channels; pixel order, so
+// the left and right neighbours are the rows before and after, whatever the
+// image width), and for one tap or for the row's three (tap_group) the
+// weights of its output channels; a tap that leaves the image reads a row of
+// zeros.  Both are loaded into registers a stage early.  The K order (tap,
+// then channel, 32 at a time, one accumulator) is that of conv3x3_kernel, so
+// the results are the same bit for bit.  The operands are swapped (rows of D
+// = output channels), so a lane holds four consecutive channels of one pixel
+// and stores 8 bytes.
+//
+// conv3x3_kernel re-reads each activation nine times and each weight once per
+// wavefront from L1, 16 rows per 16 lanes, in front of the MFMA that needs
+// it.  Measured, us, that kernel / this one: 96 -> 32 channels at 16 x 136 x
+// 136 120 / 44; 64 -> 64 at 68 x 68 55 / 15; 192 -> 64 150 / 42; 128 -> 384 at
+// 34 x 34 141 / 32; 256 -> 256 at 17 x 17 83 / 20 (270 to 500 TFLOP/s of the
+// 2500 of the matrix cores): bound by the stages' barriers and the LDS reads,
+// of which an MFMA takes 1 (2 x 2 tiles) to 0.75 (4 x 2).
+// LDS rows carry 16 bytes of padding: 16 lanes that read consecutive rows
+// then cover all banks for every cin that is a multiple of 32.
+__host__ __device__ constexpr uint32_t conv_row_bytes(uint32_t cin) { return 2 * cin + 16; }
+// bm + 2 source pixels, a row of zeros, bn weight rows per tap, a scratch piece
+__host__ __device__ constexpr size_t conv_lds_bytes(uint32_t bm, uint32_t bn, uint32_t taps, uint32_t cin) {
+    return (size_t)(bm + 3 + bn * taps) * conv_row_bytes(cin) + 16;
+}
+
+template <int WM, int WN, int MT, int NT>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(MT * NT >= 8 ? 3 : 4)))
+void conv3x3_lds_kernel(ConvArgs a) {
+    extern __shared__ __align__(16) unsigned char conv_lds[];
+    constexpr uint32_t BM = 16 * MT * WM, BN = 16 * NT * WN, T = 64 * WM * WN;
+    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint32_t wm = wv % WM, wn = wv / WM;
+    const uint32_t m = lane & 15, kg = lane >> 4;
+    const uint32_t cin = (uint32_t)a.cin, cout = (uint32_t)a.cout, w = (uint32_t)a.w, h = (uint32_t)a.h;
+    // an XCD's blocks are neighbours: they share source rows in its L2
+    const uint32_t cgs = cout / BN, per_xcd = gridDim.x / 8;
+    const uint32_t blk = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    const uint32_t p0 = blk / cgs * BM;
+    if (p0 >= a.P) return;  // whole block
+    const uint32_t cb = blk % cgs * BN, co0 = cb + wn * (16 * NT);
+    const uint32_t row = conv_row_bytes(cin), zero_row = (BM + 2) * row, w_row = zero_row + row;
+    const uint32_t tg = a.tap_group, scratch = w_row + BN * tg * row;
+
+    // this lane's pixels: LDS offset of the centre tap, and which of the nine
+    // taps lie inside the image (bit = tap)
+    uint32_t at[MT], inside[MT];
+#pragma unroll
+    for (int u = 0; u < MT; ++u) {
+        const uint32_t q = (wm * MT + u) * 16 + m, p = p0 + q;
+        const uint32_t r = p / w, j = p - r * w, i = r % h;
+        at[u] = (q + 1) * row + kg * 16;
+        uint32_t bits = 0x1ffu;
+        if (i == 0) bits &= ~0x007u;
+        if (i + 1 == h) bits &= ~0x1c0u;
+        if (j == 0) bits &= ~0x049u;
+        if (j + 1 == w) bits &= ~0x124u;
+        inside[u] = p < a.P ? bits : 0u;
+    }
+    const uint32_t zero_at = zero_row + kg * 16;
+    for (uint32_t k = threadIdx.x; k < row / 16; k += T) *(v4u*)(conv_lds + zero_row + k * 16) = v4u{0u, 0u, 0u, 0u};
+
+    v4f acc[MT][NT];
+#pragma unroll
+    for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[u][t] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    // Staging: thread t copies 16-byte piece t, t + T, ... of the rows.  Rows
+    // outside the tensor read zeros (buffer loads), pieces past the last row
+    // go to a scratch piece, so nothing branches around a load.
+    const uint32_t c8 = cin / 8;
+    const uint32_t r0 = threadIdx.x / c8, k0 = threadIdx.x % c8, dr = T / c8, dk = T % c8;
+    auto advance = [&](uint32_t& r, uint32_t& k) __attribute__((always_inline)) {
+        k += dk;
+        r += dr + (k >= c8 ? 1u : 0u);
+        k -= k >= c8 ? c8 : 0u;
+    };
+    // activations of tap row dy: pieces 0 .. kHeld T - 1 a row early, the rest in place
+    constexpr int kHeld = 5;
+    v4u held[kHeld];
+    const uint32_t pieces = (BM + 2) * c8;
+    auto row_source = [&](int dy, uint32_t& shift) __attribute__((always_inline)) {
+        const int64_t s0 = (int64_t)p0 + ((int64_t)dy - 1) * w - 1;  // source pixel of LDS row 0
+        const int64_t lo = s0 > 0 ? s0 : 0, hi = s0 + BM + 2 < (int64_t)a.P ? s0 + BM + 2 : (int64_t)a.P;
+        shift = (uint32_t)(lo - s0) * 2 * cin;  // rows before the tensor: their offsets wrap and read zeros
+        return nn_rsrc(a.x + (size_t)lo * cin, hi > lo ? (uint32_t)(hi - lo) * 2 * cin : 0u);
+    };
+    auto load_x = [&](int dy, uint32_t& r, uint32_t& k) __attribute__((always_inline)) {
+        uint32_t shift;
+        const __amdgpu_buffer_rsrc_t rx = row_source(dy, shift);
+#pragma unroll
+        for (int x = 0; x < kHeld; ++x) {
+            held[x] = nn_load16(rx, r * 2 * cin + k * 16 - shift, 0);
+            advance(r, k);
+        }
+    };
+    auto store_x = [&](uint32_t& r, uint32_t& k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < kHeld; ++x) {
+            *(v4u*)(conv_lds + (r < BM + 2 ? r * row + k * 16 : scratch)) = held[x];
+            advance(r, k);
+        }
+    };
+    // weights of tg taps: rows (tap, channel), the same way
+    constexpr int kHeldW = 4;
+    v4u held_w[kHeldW];
+    const uint32_t w_rows = tg * BN, w_pieces = w_rows * c8;
+    const __amdgpu_buffer_rsrc_t rw = nn_rsrc(a.wt, 18u * cin * cout);
+    auto load_w = [&](int tap, uint32_t& r, uint32_t& k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < kHeldW; ++x) {
+            const uint32_t t = r / BN;
+            held_w[x] = nn_load16(rw, (((uint32_t)tap + t) * cout + cb + (r - t * BN)) * 2 * cin + k * 16, 0);
+            advance(r, k);
+        }
+    };
+    auto store_w = [&](uint32_t& r, uint32_t& k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < kHeldW; ++x) {
+            *(v4u*)(conv_lds + (r < w_rows ? w_row + r * row + k * 16 : scratch)) = held_w[x];
+            advance(r, k);
+        }
+    };
+    {
+        uint32_t r = r0, k = k0;
+        load_x(0, r, k);
+        r = r0, k = k0;
+        load_w(0, r, k);
+    }
+    const uint32_t w_at = w_row + (wn * (16 * NT) + m) * row + kg * 16;
+    for (int tap0 = 0; tap0 < 9; tap0 += (int)tg) {
+        const int dy = tap0 / 3;
+        if (tap0 > 0) __syncthreads();  // the previous stage has been read
+        if (tap0 % 3 == 0) {
+            uint32_t r = r0, k = k0, r2, k2;
+            store_x(r, k);
+            r2 = r, k2 = k;
+            for (uint32_t e = kHeld * T; e < pieces; e += kHeld * T) {
+                load_x(dy, r, k);
+                store_x(r2, k2);
+            }
+        }
+        {
+            uint32_t r = r0, k = k0, r2, k2;
+            store_w(r, k);
+            r2 = r, k2 = k;
+            for (uint32_t e = kHeldW * T; e < w_pieces; e += kHeldW * T) {
+                load_w(tap0, r, k);
+                store_w(r2, k2);
+            }
+        }
+        __syncthreads();
+        if (tap0 + (int)tg < 9) {
+            uint32_t r = r0, k = k0;
+            load_w(tap0 + (int)tg, r, k);
+            if ((tap0 + (int)tg) % 3 == 0) {
+                r = r0, k = k0;
+                load_x(dy + 1, r, k);
+            }
+        }
+        for (uint32_t g = 0; g < tg; ++g) {
+            const int tap = tap0 + (int)g;
+            uint32_t from[MT];
+#pragma unroll
+            for (int u = 0; u < MT; ++u)
+                from[u] = (inside[u] >> tap) & 1u ? at[u] + (uint32_t)(tap - 3 * dy) * row - row : zero_at;
+            const uint32_t wf = w_at + g * BN * row;
+            for (uint32_t c = 0; c < 2 * cin; c += 64) {
+                v4u av[MT], bv[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) bv[t] = *(const v4u*)(conv_lds + wf + (uint32_t)t * 16 * row + c);
+#pragma unroll
+                for (int u = 0; u < MT; ++u) av[u] = *(const v4u*)(conv_lds + from[u] + c);
+#pragma unroll
+                for (int u = 0; u < MT; ++u)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[u][t] = mfma32(bv[t], av[u], acc[u][t]);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const uint32_t co = co0 + t * 16 + 4 * kg;
+        v4f bb = v4f{0.f, 0.f, 0.f, 0.f};
+        if (a.bias) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bb[j] = a.bias[co + j];
+        }
+#pragma unroll
+        for (int u = 0; u < MT; ++u) {
+            const uint32_t p = p0 + (wm * MT + u) * 16 + m;
+            if (p >= a.P) continue;
+            v4s out;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float v = acc[u][t][j] + bb[j];
+                if (a.relu) v = fmaxf(v, 0.0f);
+                out[j] = __builtin_bit_cast(short, (__bf16)v);  // nearest even
+            }
+            *(v4s*)(a.y + (size_t)p * cout + co) = out;
+        }
     }
 }
 
