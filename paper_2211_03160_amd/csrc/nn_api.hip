@@ -130,33 +130,42 @@ lbm_status lbm_nn_conv3x3_wgrad(const uint16_t* x, const uint16_t* dz, int32_t n
     if (!pos(n) || !pos(h) || !pos(w) || !pos(cin) || !pos(cout) || cin % 16 || cout % 16 || chunks < 1 ||
         chunks > 4096)
         return nn_fail(LBM_E_INVALID, "conv3x3_wgrad: bad shape");
-    const uint32_t P = (uint32_t)n * h * w;
-    uint32_t per = (P + chunks - 1) / chunks;
-    per = (per + 31) / 32 * 32;  // whole 32-pixel steps of the MFMA
-    const uint32_t used = (P + per - 1) / per;  // chunks that hold pixels
-    WGradArgs a{x, dz, partial, n, h, w, cin, cout, P, per, used};
-    const size_t waves = (size_t)used * 9 * (cout / 16) * ((cin + 63) / 64);
+    if (db && cout > 256) return nn_fail(LBM_E_INVALID, "conv3x3_wgrad: bias gradient needs cout <= 256");
+    WGradArgs a{x, dz, partial, nullptr, n, h, w, cin, cout, 0, 0, 0, 0, 0};
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(wgrad_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a);
+    const size_t count = (size_t)9 * cout * cin;
+    auto go = [&](auto wco, auto wci, auto wk, auto kx) {
+        constexpr int WCO = decltype(wco)::value, WCI = decltype(wci)::value, WK = decltype(wk)::value,
+                      KX = decltype(kx)::value;
+        a.tiles_x = ((uint32_t)w + 8 * KX - 1) / (8 * KX);
+        a.tiles_y = ((uint32_t)h + kWgTileH - 1) / kWgTileH;
+        a.tiles = (uint32_t)n * a.tiles_x * a.tiles_y;
+        // with a bias gradient the last chunk's place holds its partial sums
+        // (9 cin >= 144 per channel), unless one chunk writes db itself
+        uint32_t want = std::min<uint32_t>((uint32_t)chunks, a.tiles);
+        if (db && chunks > 1) want = std::min<uint32_t>({want, (uint32_t)chunks - 1, 9u * (uint32_t)cin});
+        a.per = (a.tiles + want - 1) / want;
+        a.chunks = (a.tiles + a.per - 1) / a.per;
+        a.bias = !db ? nullptr : a.chunks == 1 ? db : partial + (size_t)(chunks - 1) * count;
+        const uint32_t blocks = a.chunks * (uint32_t)((cout + 32 * WCO - 1) / (32 * WCO)) *
+                                (uint32_t)((cin + 32 * WCI - 1) / (32 * WCI));
+        hipLaunchKernelGGL((wgrad_kernel<WCO, WCI, WK, KX>), dim3((blocks + 7) / 8 * 8), dim3(256), 0, s, a);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    // 64 channels share a staged tile where there are as many
+    if (cout >= 64 && cin >= 64) go(I2{}, I2{}, I1{}, I1{});
+    else if (cout >= 64) go(I2{}, I1{}, I2{}, I1{});
+    else if (cin >= 64) go(I1{}, I2{}, I2{}, I1{});
+    else go(I1{}, I1{}, I4{}, I2{});
     lbm_status st = launched("conv3x3_wgrad");
     if (st) return st;
-    const size_t count = (size_t)9 * cout * cin;
-    hipLaunchKernelGGL(sum_chunks_kernel, dim3(grid1(count)), dim3(256), 0, s, (const float*)partial, used, count, dw);
-    if ((st = launched("conv3x3_wgrad sum"))) return st;
-    if (db) {
-        // the partial buffer is free again (stream order): bias sums of the
-        // same pixel chunks, then added in chunk order
-        // ranges of about 512 pixels (enough blocks to fill the GPU), at most
-        // as many partial sums as the scratch holds (9 cin >= 144 per chunk)
-        if (cout > 256) return nn_fail(LBM_E_INVALID, "conv3x3_wgrad: bias gradient needs cout <= 256");
-        const uint32_t nb_want = std::min<uint32_t>((P + 511) / 512, 144u * used);
-        const uint32_t per_b = (P + nb_want - 1) / nb_want, nb = (P + per_b - 1) / per_b;
-        hipLaunchKernelGGL(bias_partial_kernel, dim3(nb), dim3(256), 0, s, dz, P, cout, per_b, partial);
-        if ((st = launched("conv3x3_wgrad bias"))) return st;
-        hipLaunchKernelGGL(bias_sum_kernel, dim3((unsigned)cout), dim3(256), 0, s, (const float*)partial, nb, cout, db);
-        if ((st = launched("conv3x3_wgrad bias sum"))) return st;
-    }
-    return LBM_OK;
+    const bool sum_bias = db && a.chunks > 1;
+    const SumChunksArgs sa{partial, dw, (uint32_t)count, a.chunks, a.bias, db, sum_bias ? (uint32_t)cout : 0u};
+    const unsigned grid = (unsigned)((count + 63) / 64 + (sum_bias ? (cout + 63) / 64 : 0));
+    hipLaunchKernelGGL(sum_chunks_kernel, dim3(grid), dim3(256), 0, s, sa);
+    return launched("conv3x3_wgrad sum");
 }
 
 lbm_status lbm_nn_relu_backward(const uint16_t* y, const uint16_t* dy, uint16_t* dz, int64_t count, void* stream) {

@@ -346,156 +346,233 @@ __global__ void wflip_kernel(const uint16_t* wt, uint16_t* wf, int32_t cin, int3
 }
 
 struct WGradArgs {
-    const uint16_t* x;   // [P][cin]
-    const uint16_t* dz;  // [P][cout]
+    const uint16_t* x;   // [n][h][w][cin]
+    const uint16_t* dz;  // [n][h][w][cout]
     float* partial;      // [chunks][9][cout][cin]
+    float* bias;         // [chunks][cout], or null
     int32_t n, h, w, cin, cout;
-    uint32_t P, chunk;   // pixels per chunk (multiple of 32)
-    uint32_t chunks;
+    uint32_t tiles_x, tiles_y, tiles;  // pixel tiles per image row and column, of all images
+    uint32_t per, chunks;              // tiles per chunk, chunks
 };
 
-// dW[tap][co][ci] = sum_p dz[p][co] x[p shifted by tap][ci]: M = co,
-// N = ci (4 tiles per wave), K = pixels of one chunk, 32 per instruction.
-// Both operands are stored pixel-major, so a lane's eight consecutive
-// pixels of one channel are 2 cout (2 cin) bytes apart: every K step loads
-// the 32-pixel tiles with 16-byte loads (8 channels of one pixel per lane)
-// and writes them transposed into the wavefront's own LDS area, from which
-// each operand fragment is one 16-byte read.  (A wavefront's LDS accesses
-// execute in order, so no barrier is needed: the wavefronts of a block
-// share nothing.)
-constexpr int kWgPad = 40;  // LDS row of 32 pixels plus 8 (spreads the banks of the fragment reads)
-struct WgradLds {
-    uint16_t a[16][kWgPad];  // dz tile, [co][pixel]
-    uint16_t b[64][kWgPad];  // x tile, [ci][pixel]
-};
-__global__ __launch_bounds__(256) void wgrad_kernel(WGradArgs a) {
-    __shared__ WgradLds lds[4];
+// dW[tap][co][ci] = sum_p dz[p][co] x[p shifted by tap][ci] and db[co] =
+// sum_p dz[p][co], on the matrix cores with K = pixels: 8 x 4 of them per
+// instruction.  A wavefront holds 32 x 32 channels of all nine taps (144
+// accumulators), so a pixel tile staged once in LDS, x with its halo, serves
+// 36 MFMAs per K step.  Both tensors are pixel-major; the operand fragments
+// (eight pixels of one channel per lane) come from LDS through the
+// transposing read: of the 16 lanes of a group, lanes 4r .. 4r + 3 point at
+// the 16 channels of pixel r, and lane i receives channel i of the four
+// pixels.  A tap is then an offset of whole pixels.  Pixels outside the image
+// are zeros in both tiles.  The block's WCO x WCI wavefronts tile the
+// channels, WK of them split the K steps and add their sums at the end; the
+// chunks (runs of tiles) are summed by sum_chunks_kernel.  The bias gradient
+// is one more MFMA against ones.
+//
+// The kernel this replaced ran one tap per wavefront: it loaded both operands
+// nine times and transposed them through 16-bit LDS writes.  us before /
+// after, sums included: 32 -> 32 channels at 16 x 136 x 136 156 / 31, 96 -> 32
+// 202 / 42, 64 -> 64 at 68 x 68 96 / 27, 256 -> 256 at 17 x 17 103 / 34.  Bound
+// by the latency of a tile's loads and the partial sums' traffic: two
+// wavefronts per SIMD (the accumulators) hold few tiles in flight.
+// LDS pixels carry 32 bytes of padding, so four consecutive pixels of a
+// transposing read fall into different banks.
+using lds_v4s = __attribute__((address_space(3))) v4s;
+__device__ __forceinline__ v4u lds_transposed(const unsigned char* p, uint32_t next) {
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + next));
+    struct P { v4s lo, hi; } r{lo, hi};
+    return __builtin_bit_cast(v4u, r);
+}
+
+constexpr int kWgTileH = 16;  // rows of a pixel tile (four K steps)
+template <int WCO, int WCI, int WK, int KX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void wgrad_kernel(WGradArgs a) {
+    static_assert(WCO * WCI * WK == 4, "four wavefronts");
+    constexpr int TW = 8 * KX, TH = kWgTileH, COB = 32 * WCO, CIB = 32 * WCI;
+    constexpr uint32_t SD = COB * 2 + 32, SX = CIB * 2 + 32;  // bytes per LDS pixel
+    constexpr int ND = TW * TH * (COB / 8), NX = (TW + 2) * (TH + 2) * (CIB / 8);  // 16-byte pieces
+    constexpr int PD = (ND + 255) / 256, PX = (NX + 255) / 256;
+    constexpr uint32_t kXAt = TW * TH * SD, kTileBytes = kXAt + (TW + 2) * (TH + 2) * SX;
+    constexpr uint32_t kSumBytes = WCO * WCI * 64 * 48 * 4;  // three taps of one wavefront per channel tile
+    __shared__ __align__(16) unsigned char lds[kTileBytes > kSumBytes || WK == 1 ? kTileBytes : kSumBytes];
     const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint32_t gw = blockIdx.x * 4 + wv;
-    // input channels in groups of up to four 16-wide tiles per wavefront
-    const uint32_t cot = (uint32_t)a.cout / 16, cit = ((uint32_t)a.cin + 63) / 64;
-    const uint32_t per_chunk = 9 * cot * cit;
-    if (gw >= per_chunk * a.chunks) return;  // whole wavefront
-    WgradLds& L = lds[wv];
-    const uint32_t chunk = gw / per_chunk, r = gw % per_chunk;
-    const uint32_t tap = r / (cot * cit), cb = (r / cit) % cot, ib = r % cit;
-    const int rest = a.cin / 16 - (int)ib * 4;
-    const int NTc = rest < 4 ? rest : 4;
-    const int32_t di = (int32_t)tap / 3 - 1, dj = (int32_t)tap % 3 - 1;
-    const uint32_t m = lane & 15, kg = lane >> 4;
-    // this lane's share of the tile loads: pixel pl of the step, channels ch8 .. ch8 + 7
-    const uint32_t pl = lane >> 1, ch8 = (lane & 1) * 8;
-    v4f acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
-    const uint32_t p_begin = chunk * a.chunk;
-    const uint32_t p_end = p_begin + a.chunk < a.P ? p_begin + a.chunk : a.P;
-    for (uint32_t p0 = p_begin; p0 < p_end; p0 += 32) {
-        const uint32_t p = p0 + pl;
-        v4u dv = v4u{0u, 0u, 0u, 0u};
-        v4u xv[4] = {v4u{0u, 0u, 0u, 0u}, v4u{0u, 0u, 0u, 0u}, v4u{0u, 0u, 0u, 0u}, v4u{0u, 0u, 0u, 0u}};
-        if (p < p_end) {
-            dv = *(const v4u*)(a.dz + (size_t)p * a.cout + cb * 16 + ch8);
-            const int32_t pj = (int32_t)(p % a.w), pi = (int32_t)((p / a.w) % a.h);
-            const int32_t pn = (int32_t)(p / ((uint32_t)a.w * a.h));
-            const int32_t si = pi + di, sj = pj + dj;
-            if (si >= 0 && si < a.h && sj >= 0 && sj < a.w) {
-                const uint16_t* xs = a.x + (size_t)((pn * a.h + si) * a.w + sj) * a.cin + ib * 64 + ch8;
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (t < NTc) xv[t] = *(const v4u*)(xs + t * 16);
-            }
-        }
-        // transposed into LDS: channel-major rows of 32 pixels
-        {
-            const uint16_t* d = (const uint16_t*)&dv;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) L.a[ch8 + j][pl] = d[j];
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (t < NTc) {
-                const uint16_t* xx = (const uint16_t*)&xv[t];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) L.b[t * 16 + ch8 + j][pl] = xx[j];
-            }
-        }
-        const v4u a8 = *(const v4u*)&L.a[m][8 * kg];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (t < NTc) acc[t] = mfma32(a8, *(const v4u*)&L.b[t * 16 + m][8 * kg], acc[t]);
-    }
-    float* out = a.partial + ((size_t)chunk * 9 + tap) * a.cout * a.cin;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        if (t < NTc) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t co = cb * 16 + 4 * kg + j;
-                const uint32_t ci = (ib * 4 + t) * 16 + m;
-                out[(size_t)co * a.cin + ci] = acc[t][j];
-            }
-        }
-    }
-}
+    const uint32_t wco = wv % WCO, wci = wv / WCO % WCI, wk = wv / (WCO * WCI);
+    const uint32_t i = lane & 15, kg = lane >> 4;
+    const uint32_t cot = ((uint32_t)a.cout + COB - 1) / COB, cit = ((uint32_t)a.cin + CIB - 1) / CIB;
+    // an XCD's blocks are neighbours: the channel tiles of one chunk share its pixels in the L2
+    const uint32_t per_xcd = gridDim.x / 8, blk = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    const uint32_t chunk = blk / (cot * cit), cb = blk % cot, ib = blk / cot % cit;
+    if (chunk >= a.chunks) return;  // whole block
+    const uint32_t t_begin = chunk * a.per, t_end = min(t_begin + a.per, a.tiles);
 
-// sum the chunk partials in chunk order: dw[e] = sum_c partial[c][e]
-__global__ void sum_chunks_kernel(const float* partial, uint32_t chunks, size_t count, float* dw) {
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < count; e += (size_t)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (uint32_t c = 0; c < chunks; ++c) s += partial[(size_t)c * count + e];
-        dw[e] = s;
-    }
-}
-
-// db[co] = sum_p dz[p][co] in two passes with a fixed reduction order.
-// Pass 1: block c sums pixels [c per, (c + 1) per) of every channel into
-// partial[c][co]: thread t takes channels 8 (t % G) .. + 7 (G = cout / 8
-// groups, one 16-byte load) of every R-th pixel (R = 256 / G rows side by
-// side, so a row is one contiguous read), then the R row sums are added in
-// order.  Pass 2 is bias_sum_kernel over the blocks.
-__global__ __launch_bounds__(256) void bias_partial_kernel(const uint16_t* dz, uint32_t P, int32_t cout,
-                                                           uint32_t per, float* partial) {
-    __shared__ float lds[256 * 8];
-    const uint32_t G = (uint32_t)cout / 8, R = 256u / G;
-    const uint32_t t = threadIdx.x, grp = t % G, row = t / G;
-    const uint32_t p0 = blockIdx.x * per, p1 = p0 + per < P ? p0 + per : P;
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (row < R) {
-        for (uint32_t p = p0 + row; p < p1; p += R) {
-            const v4u v = *(const v4u*)(dz + (size_t)p * cout + grp * 8);
-            const uint16_t* h = (const uint16_t*)&v;
+    v4f acc[9][2][2], accb[2];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) s[j] += bf2f(h[j]);
+    for (int u = 0; u < 2; ++u) {
+        accb[u] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) acc[tap][u][t] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    v4u ones;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ones[k] = 0x3f803f80u;
+    const bool with_bias = a.bias && ib == 0 && wci == 0;
+
+    v4u dv[PD], xv[PX];
+    uint32_t tx = 0, ty = 0;
+    auto load = [&](uint32_t t) __attribute__((always_inline)) {
+        const uint32_t img = t / (a.tiles_x * a.tiles_y), r2 = t - img * (a.tiles_x * a.tiles_y);
+        const int32_t y0 = (int32_t)(r2 / a.tiles_x) * TH, x0 = (int32_t)(r2 % a.tiles_x) * TW;
+        const size_t base = (size_t)img * a.h * a.w;
+#pragma unroll
+        for (int p = 0; p < PD; ++p) {
+            const int e = p * 256 + (int)threadIdx.x, px = e / (COB / 8), k = e % (COB / 8);
+            const int32_t y = y0 + px / TW, x = x0 + px % TW, ch = (int32_t)cb * COB + k * 8;
+            dv[p] = v4u{0u, 0u, 0u, 0u};
+            if (e < ND && y < a.h && x < a.w && ch < a.cout)
+                dv[p] = *(const v4u*)(a.dz + (base + (size_t)y * a.w + x) * a.cout + ch);
         }
-    }
-    if (row < R) {  // (256 % G threads beyond the last row hold nothing)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) lds[row * (uint32_t)cout + grp * 8 + j] = s[j];
-    }
-    __syncthreads();
-    if (t < (uint32_t)cout) {
-        float v = 0.0f;
-        for (uint32_t k = 0; k < R; ++k) v += lds[k * (uint32_t)cout + t];
-        partial[(size_t)blockIdx.x * cout + t] = v;
-    }
-}
-
-// Pass 2 of the bias gradient: db[co] = sum over the nb partial sums of
-// channel co, one block per channel: thread t adds partials t, t + 256, ...
-// in order, then the 256 sums are added pairwise in a fixed tree.
-__global__ __launch_bounds__(256) void bias_sum_kernel(const float* partial, uint32_t nb, int32_t cout, float* db) {
-    __shared__ float lds[256];
-    const uint32_t co = blockIdx.x, t = threadIdx.x;
-    float s = 0.0f;
-    for (uint32_t b = t; b < nb; b += 256) s += partial[(size_t)b * cout + co];
-    lds[t] = s;
-    __syncthreads();
-    for (uint32_t o = 128; o > 0; o >>= 1) {
-        if (t < o) lds[t] += lds[t + o];
+        for (int p = 0; p < PX; ++p) {
+            const int e = p * 256 + (int)threadIdx.x, px = e / (CIB / 8), k = e % (CIB / 8);
+            const int32_t y = y0 - 1 + px / (TW + 2), x = x0 - 1 + px % (TW + 2), ch = (int32_t)ib * CIB + k * 8;
+            xv[p] = v4u{0u, 0u, 0u, 0u};
+            if (e < NX && y >= 0 && y < a.h && x >= 0 && x < a.w && ch < a.cin)
+                xv[p] = *(const v4u*)(a.x + (base + (size_t)y * a.w + x) * a.cin + ch);
+        }
+    };
+    load(t_begin);
+    for (uint32_t t = t_begin; t < t_end; ++t) {
+        if (t > t_begin) __syncthreads();  // the previous tile has been read
+#pragma unroll
+        for (int p = 0; p < PD; ++p) {
+            const uint32_t e = p * 256 + threadIdx.x;
+            if (ND % 256 == 0 || e < ND) *(v4u*)(lds + e / (COB / 8) * SD + e % (COB / 8) * 16) = dv[p];
+        }
+#pragma unroll
+        for (int p = 0; p < PX; ++p) {
+            const uint32_t e = p * 256 + threadIdx.x;
+            if (NX % 256 == 0 || e < NX) *(v4u*)(lds + kXAt + e / (CIB / 8) * SX + e % (CIB / 8) * 16) = xv[p];
+        }
         __syncthreads();
+        const uint32_t r2 = t % (a.tiles_x * a.tiles_y);
+        ty = r2 / a.tiles_x;
+        tx = r2 % a.tiles_x;
+        if (t + 1 < t_end) load(t + 1);
+        for (uint32_t ks = wk; ks < KX * (TH / 4); ks += WK) {
+            const uint32_t kx = ks % KX * 8, ky = ks / KX * 4;
+            if (ty * TH + ky >= (uint32_t)a.h || tx * TW + kx >= (uint32_t)a.w) continue;  // all outside
+            const unsigned char* pd = lds + ((ky + kg) * TW + kx + (i >> 2)) * SD + wco * 64 + (i & 3) * 8;
+            const unsigned char* px = lds + kXAt + ((ky + kg) * (TW + 2) + kx + (i >> 2)) * SX + wci * 64 + (i & 3) * 8;
+            v4u av[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) av[u] = lds_transposed(pd + u * 32, 4 * SD);
+            if (with_bias) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) accb[u] = mfma32(av[u], ones, accb[u]);
+            }
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const v4u bv = lds_transposed(px + (tap / 3 * (TW + 2) + tap % 3) * SX + s * 32, 4 * SX);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[tap][u][s] = mfma32(av[u], bv, acc[tap][u][s]);
+                }
+            }
+        }
     }
-    if (t == 0) db[co] = lds[0];
+    // the sums of the wavefronts that split the K steps, three taps at a time, in order
+    if constexpr (WK > 1) {
+        v4f* sum = (v4f*)lds + (size_t)(wv % (WCO * WCI)) * 64 * 12;
+#pragma unroll
+        for (int g = 0; g < 3; ++g) {
+            for (uint32_t k = 1; k < WK; ++k) {
+                __syncthreads();
+                if (wk == k) {
+#pragma unroll
+                    for (int e = 0; e < 12; ++e) sum[e * 64 + lane] = acc[g * 3 + e / 4][e / 2 % 2][e % 2];
+                }
+                __syncthreads();
+                if (wk == 0) {
+#pragma unroll
+                    for (int e = 0; e < 12; ++e) acc[g * 3 + e / 4][e / 2 % 2][e % 2] += sum[e * 64 + lane];
+                }
+            }
+        }
+        for (uint32_t k = 1; k < WK; ++k) {
+            __syncthreads();
+            if (wk == k) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) sum[e * 64 + lane] = accb[e];
+            }
+            __syncthreads();
+            if (wk == 0) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) accb[e] += sum[e * 64 + lane];
+            }
+        }
+        if (wk != 0) return;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const uint32_t co = cb * COB + wco * 32 + u * 16 + 4 * kg;
+        if (co >= (uint32_t)a.cout) continue;
+        if (with_bias && i == 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a.bias[(size_t)chunk * a.cout + co + j] = accb[u][j];
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const uint32_t ci = ib * CIB + wci * 32 + s * 16 + i;
+            if (ci >= (uint32_t)a.cin) continue;
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    a.partial[(((size_t)chunk * 9 + tap) * a.cout + co + j) * a.cin + ci] = acc[tap][u][s][j];
+        }
+    }
+}
+
+// dw[e] = sum over the chunks of partial[c][e], and db likewise: a block takes
+// 64 values, its 16 rows of threads every 16th chunk, and the row sums are
+// added in a fixed tree
+struct SumChunksArgs {
+    const float* partial;
+    float* dw;
+    uint32_t count, chunks;
+    const float* bias;
+    float* db;
+    uint32_t bias_count;
+};
+__global__ __launch_bounds__(256) void sum_chunks_kernel(SumChunksArgs a) {
+    __shared__ v4f lds[256];
+    const uint32_t col = threadIdx.x & 15, part = threadIdx.x >> 4, blocks_w = (a.count + 63) / 64;
+    const bool w = blockIdx.x < blocks_w;
+    const float* src = w ? a.partial : a.bias;
+    float* dst = w ? a.dw : a.db;
+    const uint32_t count = w ? a.count : a.bias_count;
+    const uint32_t e = (blockIdx.x - (w ? 0 : blocks_w)) * 64 + col * 4;  // counts are multiples of 16
+    v4f s = v4f{0.f, 0.f, 0.f, 0.f};
+    if (e < count)
+        for (uint32_t c = part; c < a.chunks; c += 16) {
+            const float* p = src + (size_t)c * count + e;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s[j] += p[j];
+        }
+    lds[threadIdx.x] = s;
+    for (uint32_t o = 128; o >= 16; o >>= 1) {
+        __syncthreads();
+        if (threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
+    }
+    if (part == 0 && e < count) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dst[e + j] = lds[threadIdx.x][j];
+    }
 }
 
 __global__ void relu_backward_kernel(const uint16_t* y, const uint16_t* dy, uint16_t* dz, size_t count) {

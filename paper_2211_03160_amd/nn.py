@@ -99,8 +99,14 @@ def conv3x3_flip(wt, cin, cout):
 def conv3x3_wgrad(x, dz, cout, dw, db):
     import torch
     n, h, w, cin = x.shape
-    P = n * h * w
-    chunks = int(max(1, min(64, P // 2048)))
+    # enough chunks to fill the GPU with the blocks of the channel tiles (64
+    # wide from 64 channels on), at least 64 pixels each and at most 256 MB of
+    # partial sums.  us at 16 x 136 x 136, 32 -> 32: 62 / 40 / 31 / 32 with 64 /
+    # 128 / 256 / 384 chunks; 16 x 17 x 17, 256 -> 256 (16 tiles): 37 / 34 / 48
+    # with 16 / 48 / 64
+    tiles = -(-cout // (64 if cout >= 64 else 32)) * -(-cin // (64 if cin >= 64 else 32))
+    chunks = max(48, min(256, 384 // tiles))
+    chunks = int(max(1, min(chunks, n * h * w // 64, (1 << 26) // (9 * cout * cin))))
     partial = torch.empty(chunks * 9 * cout * cin, dtype=torch.float32, device="cuda")
     _check(lib().lbm_nn_conv3x3_wgrad(_p(x), _p(dz), n, h, w, cin, cout, _p(partial), chunks,
                                       _p(dw), _p(db), _s()))

@@ -36,3 +36,31 @@ def test_conv3x3_lds_blocks(n, h, w, ci, co):
         ref = R.relu(ref) if relu else ref
         err = np.abs(_host(nn.conv3x3(xd, wd, bias, co, relu)) - ref)
         assert np.all(err <= BF * np.abs(ref) + 1e-5 * scale), err.max()
+
+
+# channel tiles of 32 and 64 on either side, ragged ones, pixel tiles one off
+# their 8 x 16 (16 x 16 with 32 channels), one chunk, a chunk per tile and more
+@pytest.mark.parametrize("chunks", [1, 2, 5, 400])
+@pytest.mark.parametrize("n,h,w,ci,co", [(2, 17, 15, 32, 32), (1, 16, 17, 16, 48), (3, 15, 9, 64, 32),
+                                         (2, 5, 24, 32, 64), (1, 33, 8, 80, 80), (2, 9, 7, 128, 96), (1, 1, 1, 16, 16)])
+def test_conv3x3_wgrad_tiles(n, h, w, ci, co, chunks):
+    """FP32 sums of exact BF16 products: within 1e-5 of the sum of |terms|."""
+    import torch
+    from paper_2211_03160_amd import nn
+    rng = np.random.default_rng(ci + co + chunks)
+    x = _bf(rng.standard_normal((n, h, w, ci)))
+    dz = _bf(rng.standard_normal((n, h, w, co)))
+    xd, dzd = _dev_bf16(x), _dev_bf16(dz)
+    zero = np.zeros((3, 3, ci, co))
+    _, ref, bref = R.conv3x3_backward(x, zero, dz)
+    _, scale, bscale = R.conv3x3_backward(np.abs(x), zero, np.abs(dz))
+    partial = torch.full((chunks * 9 * co * ci,), float("nan"), device="cuda")
+    for with_bias in (True, False):
+        dw = torch.full((9, co, ci), float("nan"), device="cuda")
+        db = torch.full((co,), float("nan"), device="cuda")
+        nn._check(nn.lib().lbm_nn_conv3x3_wgrad(nn._p(xd), nn._p(dzd), n, h, w, ci, co, nn._p(partial), chunks,
+                                                nn._p(dw), nn._p(db) if with_bias else None, nn._s()))
+        got = dw.cpu().numpy().astype(np.float64).reshape(3, 3, co, ci).transpose(0, 1, 3, 2)
+        assert np.all(np.abs(got - ref) <= 1e-5 * scale + 1e-6)
+        if with_bias:
+            assert np.all(np.abs(db.cpu().numpy() - bref) <= 1e-5 * bscale + 1e-6)
