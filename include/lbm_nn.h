@@ -41,6 +41,18 @@ lbm_status lbm_nn_conv3x3(const uint16_t* x, int32_t n, int32_t h, int32_t w, in
 lbm_status lbm_nn_conv3x3_flip(const uint16_t* wt, int32_t cin, int32_t cout, uint16_t* wf,
                                void* stream);
 
+/* lbm_nn_conv3x3_flip of `count` layers in one launch: host arrays of
+ * device pointers and channel counts.                                   */
+lbm_status lbm_nn_conv3x3_flip_many(int32_t count, const uint16_t* const* wt, const int32_t* cin,
+                                    const int32_t* cout, uint16_t* const* wf, void* stream);
+
+/* lbm_nn_conv3x3 without bias and ReLU, and 0 where mask [n,h,w,cout] is not
+ * positive: with flipped weights and the mask of the ReLU output that fed
+ * the convolution, the gradient in front of that ReLU.                  */
+lbm_status lbm_nn_conv3x3_masked(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cin,
+                                 const uint16_t* wt, const uint16_t* mask, int32_t cout,
+                                 uint16_t* y, void* stream);
+
 /* Weight and bias gradients of a convolution with input x [n,h,w,cin] and
  * output gradient dz [n,h,w,cout]: dw [9][cout][cin] and db [cout] (FP32;
  * db may be NULL; with db, cout <= 256).  `partial` is scratch of
@@ -68,6 +80,25 @@ lbm_status lbm_nn_upsample2(const uint16_t* x, int32_t n, int32_t h, int32_t w, 
                             uint16_t* y, void* stream);
 lbm_status lbm_nn_upsample2_backward(const uint16_t* dy, int32_t n, int32_t h, int32_t w,
                                      int32_t c, uint16_t* dx, void* stream);
+
+/* The joins of a U-Net, one pass each; channel counts multiples of 8,
+ * tensors 16-byte aligned (else LBM_E_INVALID).
+ * upsample2_concat: y [n,2h,2w,cx+cs] = x [n,h,w,cx] upsampled beside skip
+ *   [n,2h,2w,cs].
+ * upsample2_concat_backward: dx [n,h,w,c] = 2x2 sums of the first c channels
+ *   of dy [n,2h,2w,cd], 0 where mask [n,h,w,c] is not positive (mask NULL:
+ *   no mask).
+ * avgpool2_backward_add: dx [n,h,w,c] = gradient of the pooling from dy
+ *   [n,h/2,w/2,c], rounded, plus channels aoff .. aoff+c-1 of add
+ *   [n,h,w,ca] (add NULL: nothing), 0 where mask is not positive.       */
+lbm_status lbm_nn_upsample2_concat(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cx,
+                                   const uint16_t* skip, int32_t cs, uint16_t* y, void* stream);
+lbm_status lbm_nn_upsample2_concat_backward(const uint16_t* dy, int32_t n, int32_t h, int32_t w,
+                                            int32_t c, int32_t cd, const uint16_t* mask,
+                                            uint16_t* dx, void* stream);
+lbm_status lbm_nn_avgpool2_backward_add(const uint16_t* dy, int32_t n, int32_t h, int32_t w,
+                                        int32_t c, const uint16_t* add, int32_t ca, int32_t aoff,
+                                        const uint16_t* mask, uint16_t* dx, void* stream);
 
 /* Channel slice copy for concatenation and its gradient:
  * dst[p][doff + k] = src[p][soff + k] (or += when accumulate != 0), k < cc,

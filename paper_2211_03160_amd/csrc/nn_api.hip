@@ -39,6 +39,19 @@ unsigned grid1(size_t n, unsigned bs = 256, unsigned cap = 65536) {
 
 bool pos(int32_t v) { return v > 0; }
 
+bool aligned16(const void* p) { return (uintptr_t)p % 16 == 0; }
+
+// the grid of the row kernels: a block row per image row of n x h, runs of
+// 256 channel groups of 8 along it.  false: channels not a multiple of 8, or
+// the grid is too large (the element kernels take those).
+bool row_grid(int64_t n, int64_t h, int64_t w, int64_t c, dim3* grid) {
+    if (c % 8 || h > 0x7fffffff / n) return false;
+    const int64_t runs = (w * (c / 8) + 255) / 256;
+    if (runs > 65535 || w * (c / 8) > 0x7fffff00) return false;
+    *grid = dim3((unsigned)(n * h), (unsigned)runs);
+    return true;
+}
+
 constexpr size_t kMaxLds = 160 * 1024;
 
 template <int WM, int WN, int MT, int NT> bool conv3x3_lds_go(ConvArgs a, uint32_t taps, hipStream_t s) {
@@ -82,14 +95,16 @@ extern "C" {
 
 const char* lbm_nn_last_error(void) { return g_nn_err; }
 
-lbm_status lbm_nn_conv3x3(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cin, const uint16_t* wt,
-                          const float* bias, int32_t cout, int32_t relu, uint16_t* y, void* stream) {
+// y = act(conv(x, wt) + bias), 0 where mask is not positive
+static lbm_status conv3x3(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cin, const uint16_t* wt,
+                          const float* bias, const uint16_t* mask, int32_t cout, int32_t relu, uint16_t* y,
+                          void* stream) {
     if (!x || !wt || !y) return nn_fail(LBM_E_INVALID, "conv3x3: null tensor");
     if (!pos(n) || !pos(h) || !pos(w) || !pos(cin) || !pos(cout) || cin % 16 || cout % 16)
         return nn_fail(LBM_E_INVALID, "conv3x3: bad shape n=%d h=%d w=%d cin=%d cout=%d", n, h, w, cin, cout);
     const double P = (double)n * h * w;
     if (P * (cin > cout ? cin : cout) > 4.0e9) return nn_fail(LBM_E_INVALID, "conv3x3: tensor too large");
-    ConvArgs a{x, wt, bias, y, n, h, w, cin, cout, relu, (uint32_t)P, (uint32_t)((P + 15) / 16), 0};
+    ConvArgs a{x, wt, bias, mask, y, n, h, w, cin, cout, relu, (uint32_t)P, (uint32_t)((P + 15) / 16), 0};
     if (conv3x3_lds(a, (hipStream_t)stream)) return launched("conv3x3");
     const int NT = cout % 64 == 0 ? 4 : cout % 32 == 0 ? 2 : 1;
     // pixel tiles per wavefront: as many as keep at least 4096 wavefronts
@@ -116,11 +131,45 @@ lbm_status lbm_nn_conv3x3(const uint16_t* x, int32_t n, int32_t h, int32_t w, in
     return launched("conv3x3");
 }
 
+lbm_status lbm_nn_conv3x3(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cin, const uint16_t* wt,
+                          const float* bias, int32_t cout, int32_t relu, uint16_t* y, void* stream) {
+    return conv3x3(x, n, h, w, cin, wt, bias, nullptr, cout, relu, y, stream);
+}
+
+lbm_status lbm_nn_conv3x3_masked(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cin, const uint16_t* wt,
+                                 const uint16_t* mask, int32_t cout, uint16_t* y, void* stream) {
+    if (!mask) return nn_fail(LBM_E_INVALID, "conv3x3_masked: null mask");
+    return conv3x3(x, n, h, w, cin, wt, nullptr, mask, cout, 0, y, stream);
+}
+
+lbm_status lbm_nn_conv3x3_flip_many(int32_t count, const uint16_t* const* wt, const int32_t* cin, const int32_t* cout,
+                                    uint16_t* const* wf, void* stream) {
+    if (count < 0 || (count && (!wt || !cin || !cout || !wf)))
+        return nn_fail(LBM_E_INVALID, "conv3x3_flip: bad arguments");
+    for (int32_t k = 0; k < count; ++k)
+        if (!wt[k] || !wf[k] || !pos(cin[k]) || !pos(cout[k]))
+            return nn_fail(LBM_E_INVALID, "conv3x3_flip: bad arguments");
+    for (int32_t k0 = 0; k0 < count; k0 += kFlipMost) {
+        FlipArgs a{};
+        a.count = std::min(count - k0, kFlipMost);
+        for (int32_t k = 0; k < a.count; ++k) {
+            a.wt[k] = wt[k0 + k];
+            a.wf[k] = wf[k0 + k];
+            a.cin[k] = cin[k0 + k];
+            a.cout[k] = cout[k0 + k];
+            const uint64_t blocks = 9ull * (((uint64_t)a.cin[k] + 31) / 32) * (((uint64_t)a.cout[k] + 31) / 32);
+            if (a.first[k] + blocks > 0x7fffffffull) return nn_fail(LBM_E_INVALID, "conv3x3_flip: layer too large");
+            a.first[k + 1] = a.first[k] + (uint32_t)blocks;
+        }
+        hipLaunchKernelGGL(wflip_kernel, dim3(a.first[a.count]), dim3(256), 0, (hipStream_t)stream, a);
+        const lbm_status st = launched("conv3x3_flip");
+        if (st) return st;
+    }
+    return LBM_OK;
+}
+
 lbm_status lbm_nn_conv3x3_flip(const uint16_t* wt, int32_t cin, int32_t cout, uint16_t* wf, void* stream) {
-    if (!wt || !wf || !pos(cin) || !pos(cout)) return nn_fail(LBM_E_INVALID, "conv3x3_flip: bad arguments");
-    const size_t total = (size_t)9 * cin * cout;
-    hipLaunchKernelGGL(wflip_kernel, dim3(grid1(total)), dim3(256), 0, (hipStream_t)stream, wt, wf, cin, cout);
-    return launched("conv3x3_flip");
+    return lbm_nn_conv3x3_flip_many(1, &wt, &cin, &cout, &wf, stream);
 }
 
 lbm_status lbm_nn_conv3x3_wgrad(const uint16_t* x, const uint16_t* dz, int32_t n, int32_t h, int32_t w,
@@ -170,8 +219,10 @@ lbm_status lbm_nn_conv3x3_wgrad(const uint16_t* x, const uint16_t* dz, int32_t n
 
 lbm_status lbm_nn_relu_backward(const uint16_t* y, const uint16_t* dy, uint16_t* dz, int64_t count, void* stream) {
     if (!y || !dy || !dz || count < 0) return nn_fail(LBM_E_INVALID, "relu_backward: bad arguments");
-    hipLaunchKernelGGL(relu_backward_kernel, dim3(grid1(count)), dim3(256), 0, (hipStream_t)stream, y, dy, dz,
-                       (size_t)count);
+    const size_t groups = aligned16(y) && aligned16(dy) && aligned16(dz) ? (size_t)count / 8 : 0;
+    const size_t threads = std::max<size_t>(groups, (size_t)count - groups * 8);
+    hipLaunchKernelGGL(relu_backward_kernel, dim3(grid1(threads)), dim3(256), 0, (hipStream_t)stream, y, dy, dz,
+                       groups, (size_t)count);
     return launched("relu_backward");
 }
 
@@ -179,8 +230,13 @@ lbm_status lbm_nn_avgpool2(const uint16_t* x, int32_t n, int32_t h, int32_t w, i
                            void* stream) {
     if (!x || !y || !pos(n) || !pos(h) || !pos(w) || !pos(c) || h % 2 || w % 2)
         return nn_fail(LBM_E_INVALID, "avgpool2: bad arguments");
-    hipLaunchKernelGGL(avgpool2_kernel, dim3(grid1((size_t)n * h * w * c / 4)), dim3(256), 0, (hipStream_t)stream,
-                       x, y, n, h, w, c);
+    dim3 grid;
+    if (aligned16(x) && aligned16(y) && row_grid(n, h / 2, w / 2, c, &grid))
+        hipLaunchKernelGGL(pool_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, y, (uint32_t)h / 2, (uint32_t)w / 2,
+                           (uint32_t)c);
+    else
+        hipLaunchKernelGGL(avgpool2_kernel, dim3(grid1((size_t)n * h * w * c / 4)), dim3(256), 0, (hipStream_t)stream,
+                           x, y, n, h, w, c);
     return launched("avgpool2");
 }
 
@@ -188,26 +244,77 @@ lbm_status lbm_nn_avgpool2_backward(const uint16_t* dy, int32_t n, int32_t h, in
                                     void* stream) {
     if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c) || h % 2 || w % 2)
         return nn_fail(LBM_E_INVALID, "avgpool2_backward: bad arguments");
-    hipLaunchKernelGGL(avgpool2_backward_kernel, dim3(grid1((size_t)n * h * w * c)), dim3(256), 0,
-                       (hipStream_t)stream, dy, dx, n, h, w, c);
+    dim3 grid;
+    if (aligned16(dy) && aligned16(dx) && row_grid(n, h, w, c, &grid))
+        hipLaunchKernelGGL(pool_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, (const uint16_t*)nullptr,
+                           (const uint16_t*)nullptr, dx, (uint32_t)h, (uint32_t)w, (uint32_t)c, 0u, 0u);
+    else
+        hipLaunchKernelGGL(avgpool2_backward_kernel, dim3(grid1((size_t)n * h * w * c)), dim3(256), 0,
+                           (hipStream_t)stream, dy, dx, n, h, w, c);
     return launched("avgpool2_backward");
+}
+
+lbm_status lbm_nn_avgpool2_backward_add(const uint16_t* dy, int32_t n, int32_t h, int32_t w, int32_t c,
+                                        const uint16_t* add, int32_t ca, int32_t aoff, const uint16_t* mask,
+                                        uint16_t* dx, void* stream) {
+    dim3 grid;
+    if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c) || h % 2 || w % 2 ||
+        (add && (!pos(ca) || ca % 8 || aoff < 0 || aoff % 8 || (int64_t)aoff + c > ca)) || !aligned16(dy) ||
+        !aligned16(dx) || !aligned16(add) || !aligned16(mask) || !row_grid(n, h, w, c, &grid))
+        return nn_fail(LBM_E_INVALID, "avgpool2_backward_add: bad arguments");
+    hipLaunchKernelGGL(pool_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, add, mask, dx, (uint32_t)h,
+                       (uint32_t)w, (uint32_t)c, (uint32_t)ca, (uint32_t)aoff);
+    return launched("avgpool2_backward_add");
 }
 
 lbm_status lbm_nn_upsample2(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t c, uint16_t* y,
                             void* stream) {
     if (!x || !y || !pos(n) || !pos(h) || !pos(w) || !pos(c)) return nn_fail(LBM_E_INVALID, "upsample2: bad arguments");
-    hipLaunchKernelGGL(upsample2_kernel, dim3(grid1((size_t)n * 4 * h * w * c)), dim3(256), 0, (hipStream_t)stream,
-                       x, y, n, h, w, c);
+    dim3 grid;
+    if (aligned16(x) && aligned16(y) && row_grid(n, 2 * (int64_t)h, 2 * (int64_t)w, c, &grid))
+        hipLaunchKernelGGL(up_concat_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, (const uint16_t*)nullptr, y,
+                           2u * h, 2u * w, (uint32_t)c, 0u);
+    else
+        hipLaunchKernelGGL(upsample2_kernel, dim3(grid1((size_t)n * 4 * h * w * c)), dim3(256), 0, (hipStream_t)stream,
+                           x, y, n, h, w, c);
     return launched("upsample2");
+}
+
+lbm_status lbm_nn_upsample2_concat(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cx, const uint16_t* skip,
+                                   int32_t cs, uint16_t* y, void* stream) {
+    dim3 grid;
+    if (!x || !skip || !y || !pos(n) || !pos(h) || !pos(w) || !pos(cx) || !pos(cs) || cx % 8 || cs % 8 ||
+        !aligned16(x) || !aligned16(skip) || !aligned16(y) ||
+        !row_grid(n, 2 * (int64_t)h, 2 * (int64_t)w, (int64_t)cx + cs, &grid))
+        return nn_fail(LBM_E_INVALID, "upsample2_concat: bad arguments");
+    hipLaunchKernelGGL(up_concat_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, skip, y, 2u * h, 2u * w,
+                       (uint32_t)cx, (uint32_t)cs);
+    return launched("upsample2_concat");
 }
 
 lbm_status lbm_nn_upsample2_backward(const uint16_t* dy, int32_t n, int32_t h, int32_t w, int32_t c, uint16_t* dx,
                                      void* stream) {
     if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c))
         return nn_fail(LBM_E_INVALID, "upsample2_backward: bad arguments");
-    hipLaunchKernelGGL(upsample2_backward_kernel, dim3(grid1((size_t)n * h * w * c)), dim3(256), 0,
-                       (hipStream_t)stream, dy, dx, n, h, w, c);
+    dim3 grid;
+    if (aligned16(dy) && aligned16(dx) && row_grid(n, h, w, c, &grid))
+        hipLaunchKernelGGL(up_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, (const uint16_t*)nullptr,
+                           dx, (uint32_t)h, (uint32_t)w, (uint32_t)c, (uint32_t)c);
+    else
+        hipLaunchKernelGGL(upsample2_backward_kernel, dim3(grid1((size_t)n * h * w * c)), dim3(256), 0,
+                           (hipStream_t)stream, dy, dx, n, h, w, c);
     return launched("upsample2_backward");
+}
+
+lbm_status lbm_nn_upsample2_concat_backward(const uint16_t* dy, int32_t n, int32_t h, int32_t w, int32_t c, int32_t cd,
+                                            const uint16_t* mask, uint16_t* dx, void* stream) {
+    dim3 grid;
+    if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c) || cd < c || cd % 8 || !aligned16(dy) ||
+        !aligned16(dx) || !aligned16(mask) || !row_grid(n, h, w, c, &grid))
+        return nn_fail(LBM_E_INVALID, "upsample2_concat_backward: bad arguments");
+    hipLaunchKernelGGL(up_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, mask, dx, (uint32_t)h,
+                       (uint32_t)w, (uint32_t)c, (uint32_t)cd);
+    return launched("upsample2_concat_backward");
 }
 
 lbm_status lbm_nn_copy_channels(const uint16_t* src, int32_t cs, int32_t soff, uint16_t* dst, int32_t cd,
@@ -215,8 +322,14 @@ lbm_status lbm_nn_copy_channels(const uint16_t* src, int32_t cs, int32_t soff, u
     if (!src || !dst || !pos(cs) || !pos(cd) || !pos(cc) || soff < 0 || doff < 0 || soff + cc > cs ||
         doff + cc > cd || pixels < 0)
         return nn_fail(LBM_E_INVALID, "copy_channels: bad arguments");
-    hipLaunchKernelGGL(copy_channels_kernel, dim3(grid1((size_t)pixels * cc)), dim3(256), 0, (hipStream_t)stream,
-                       src, cs, soff, dst, cd, doff, cc, (size_t)pixels, accumulate);
+    const uint64_t items = (uint64_t)pixels * (uint32_t)(cc / 8);
+    if (!((cs | soff | cd | doff | cc) % 8) && aligned16(src) && aligned16(dst) && items < 0x80000000ull)
+        hipLaunchKernelGGL(copy_channels8_kernel, dim3(grid1((size_t)items)), dim3(256), 0, (hipStream_t)stream, src,
+                           (uint32_t)cs, (uint32_t)soff, dst, (uint32_t)cd, (uint32_t)doff, (uint32_t)cc / 8,
+                           (uint32_t)items, accumulate);
+    else
+        hipLaunchKernelGGL(copy_channels_kernel, dim3(grid1((size_t)pixels * cc)), dim3(256), 0, (hipStream_t)stream,
+                           src, cs, soff, dst, cd, doff, cc, (size_t)pixels, accumulate);
     return launched("copy_channels");
 }
 
@@ -231,7 +344,7 @@ lbm_status lbm_nn_mse(const uint16_t* y, int32_t cy, const float* target, const 
                        (float)(1.0 / count), dy, scratch);
     lbm_status st = launched("mse");
     if (st) return st;
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(64), 0, s, (const float*)scratch, (int32_t)grid,
+    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, (const float*)scratch, (int32_t)grid,
                        (float)(1.0 / count), loss);
     return launched("mse sum");
 }

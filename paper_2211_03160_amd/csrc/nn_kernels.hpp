@@ -50,6 +50,7 @@ struct ConvArgs {
     const uint16_t* x;   // [P][cin], P = n h w
     const uint16_t* wt;  // [9][cout][cin]
     const float* bias;   // [cout] or null
+    const uint16_t* mask;  // [P][cout] or null: the output is 0 where the mask is not positive
     uint16_t* y;         // [P][cout]
     int32_t n, h, w, cin, cout, relu;
     uint32_t P, ptiles;  // pixels, 16-pixel tiles
@@ -120,7 +121,8 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(ConvArgs a) {
                 if (q < a.P) {
                     float v = acc[u][t][j] + bb;
                     if (a.relu) v = fmaxf(v, 0.0f);
-                    a.y[(size_t)q * a.cout + co] = f2bf(v);
+                    const size_t e = (size_t)q * a.cout + co;
+                    a.y[e] = !a.mask || bf2f(a.mask[e]) > 0.0f ? f2bf(v) : (uint16_t)0;
                 }
             }
     }
@@ -328,21 +330,44 @@ void conv3x3_lds_kernel(ConvArgs a) {
                 if (a.relu) v = fmaxf(v, 0.0f);
                 out[j] = __builtin_bit_cast(short, (__bf16)v);  // nearest even
             }
+            if (a.mask) {
+                const v4s mk = *(const v4s*)(a.mask + (size_t)p * cout + co);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) out[j] = bf2f((uint16_t)mk[j]) > 0.0f ? out[j] : (short)0;
+            }
             *(v4s*)(a.y + (size_t)p * cout + co) = out;
         }
     }
 }
 
 // flipped, transposed weights for the data gradient:
-// wf[tap'][ci][co] = wt[8 - tap'][co][ci]
-__global__ void wflip_kernel(const uint16_t* wt, uint16_t* wf, int32_t cin, int32_t cout) {
-    const size_t total = (size_t)9 * cin * cout;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-        const int32_t co = (int32_t)(e % cout);
-        const int32_t ci = (int32_t)((e / cout) % cin);
-        const int32_t tap = (int32_t)(e / ((size_t)cout * cin));
-        wf[e] = wt[((size_t)(8 - tap) * cout + co) * cin + ci];
-    }
+// wf[tap'][ci][co] = wt[8 - tap'][co][ci], of up to kFlipMost layers in one
+// launch: a block transposes 32 x 32 values of one tap through LDS
+constexpr int kFlipMost = 32;
+struct FlipArgs {
+    const uint16_t* wt[kFlipMost];
+    uint16_t* wf[kFlipMost];
+    int32_t cin[kFlipMost], cout[kFlipMost];
+    uint32_t first[kFlipMost + 1];  // first block of each layer
+    int32_t count;
+};
+__global__ __launch_bounds__(256) void wflip_kernel(FlipArgs a) {
+    __shared__ uint16_t t[32][33];
+    int l = 0;
+    while (l + 1 < a.count && blockIdx.x >= a.first[l + 1]) ++l;
+    const uint32_t ci = (uint32_t)a.cin[l], co = (uint32_t)a.cout[l];
+    const uint32_t ti = (ci + 31) / 32, to = (co + 31) / 32, r = blockIdx.x - a.first[l];
+    const uint32_t tap = r / (ti * to), i0 = r % ti * 32, o0 = r / ti % to * 32;
+    const uint32_t x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const uint16_t* src = a.wt[l] + (size_t)(8 - tap) * co * ci;
+    uint16_t* dst = a.wf[l] + (size_t)tap * co * ci;
+#pragma unroll
+    for (uint32_t k = 0; k < 32; k += 8)
+        if (o0 + y + k < co && i0 + x < ci) t[y + k][x] = src[(size_t)(o0 + y + k) * ci + i0 + x];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < 32; k += 8)
+        if (i0 + y + k < ci && o0 + x < co) dst[(size_t)(i0 + y + k) * co + o0 + x] = t[x][y + k];
 }
 
 struct WGradArgs {
@@ -575,11 +600,138 @@ __global__ __launch_bounds__(256) void sum_chunks_kernel(SumChunksArgs a) {
     }
 }
 
-__global__ void relu_backward_kernel(const uint16_t* y, const uint16_t* dy, uint16_t* dz, size_t count) {
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < count; e += (size_t)gridDim.x * blockDim.x)
+// ------------------------------------------------- layers without products
+// Memory-bound passes over NHWC tensors.  A thread takes eight channels (16
+// bytes) of one pixel; an image row takes a run of blocks, so the position in
+// it costs one 32-bit division.  The element-per-thread kernels (below) spend
+// their time on four 64-bit divisions per value.  In one gradient of the 257^2
+// network (batch 16) the upsampling, concatenation, pooling and ReLU passes,
+// forward and backward, took 670 us in 41 launches; joined they take 115 us in
+// 12, and the ReLU masks of the others ride in the convolutions' stores.
+struct Vec8 {
+    v4u v;
+    __device__ float get(int j) const { return bf2f((uint16_t)(v[j / 2] >> (16 * (j % 2)))); }
+    __device__ void set(int j, float f) {
+        const uint32_t b = (uint32_t)f2bf(f) << (16 * (j % 2));
+        v[j / 2] = j % 2 ? (v[j / 2] & 0xffffu) | b : (v[j / 2] & 0xffff0000u) | b;
+    }
+};
+__device__ __forceinline__ Vec8 load8(const uint16_t* p) { return Vec8{*(const v4u*)p}; }
+__device__ __forceinline__ void store8(uint16_t* p, Vec8 x) { *(v4u*)p = x.v; }
+// x where the ReLU output m is positive, else 0
+__device__ __forceinline__ Vec8 relu_mask(Vec8 x, Vec8 m) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t lo = m.get(2 * j) > 0.0f ? 0x0000ffffu : 0u, hi = m.get(2 * j + 1) > 0.0f ? 0xffff0000u : 0u;
+        x.v[j] &= lo | hi;
+    }
+    return x;
+}
+// this thread's place in output row blockIdx.x = image * h + i: pixel j, channel group k of c8
+struct RowPlace {
+    uint32_t b, i, j, k;
+    bool in;
+    __device__ RowPlace(uint32_t h, uint32_t w, uint32_t c8) {
+        const uint32_t e = blockIdx.y * 256 + threadIdx.x;
+        b = blockIdx.x / h;
+        i = blockIdx.x - b * h;
+        j = e / c8;
+        k = e - j * c8;
+        in = j < w;
+    }
+};
+
+// x [n][h/2][w/2][cx] nearest-upsampled beside skip [n][h][w][cs] -> y [n][h][w][cx + cs]
+__global__ __launch_bounds__(256) void up_concat_kernel(const uint16_t* x, const uint16_t* skip, uint16_t* y,
+                                                        uint32_t h, uint32_t w, uint32_t cx, uint32_t cs) {
+    const RowPlace p(h, w, (cx + cs) / 8);
+    if (!p.in) return;
+    const size_t q = ((size_t)p.b * h + p.i) * w + p.j, k = (size_t)p.k * 8;
+    const size_t low = ((size_t)p.b * (h / 2) + p.i / 2) * (w / 2) + p.j / 2;
+    store8(y + q * (cx + cs) + k, k < cx ? load8(x + low * cx + k) : load8(skip + q * cs + (k - cx)));
+}
+
+// gradient of the upsampled part: dx [n][h][w][c] = sums of the 2x2 blocks of
+// channels 0 .. c - 1 of dy [n][2h][2w][cd], where mask (null: everywhere) is positive
+__global__ __launch_bounds__(256) void up_backward_kernel(const uint16_t* dy, const uint16_t* mask, uint16_t* dx,
+                                                          uint32_t h, uint32_t w, uint32_t c, uint32_t cd) {
+    const RowPlace p(h, w, c / 8);
+    if (!p.in) return;
+    const size_t k = (size_t)p.k * 8, q = ((size_t)p.b * h + p.i) * w + p.j, row = (size_t)2 * w * cd;
+    const uint16_t* s = dy + (((size_t)p.b * 2 * h + 2 * p.i) * 2 * w + 2 * p.j) * cd + k;
+    const Vec8 s0 = load8(s), s1 = load8(s + cd), s2 = load8(s + row), s3 = load8(s + row + cd);
+    Vec8 o{v4u{0u, 0u, 0u, 0u}};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o.set(j, s0.get(j) + s1.get(j) + s2.get(j) + s3.get(j));
+    if (mask) o = relu_mask(o, load8(mask + q * c + k));
+    store8(dx + q * c + k, o);
+}
+
+// x [n][h][w][c] -> y [n][h/2][w/2][c], 2x2 means; h, w of y
+__global__ __launch_bounds__(256) void pool_kernel(const uint16_t* x, uint16_t* y, uint32_t h, uint32_t w, uint32_t c) {
+    const RowPlace p(h, w, c / 8);
+    if (!p.in) return;
+    const size_t k = (size_t)p.k * 8, row = (size_t)2 * w * c;
+    const uint16_t* s = x + (((size_t)p.b * 2 * h + 2 * p.i) * 2 * w + 2 * p.j) * c + k;
+    const Vec8 s0 = load8(s), s1 = load8(s + c), s2 = load8(s + row), s3 = load8(s + row + c);
+    Vec8 o{v4u{0u, 0u, 0u, 0u}};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o.set(j, 0.25f * (s0.get(j) + s1.get(j) + s2.get(j) + s3.get(j)));
+    store8(y + (((size_t)p.b * h + p.i) * w + p.j) * c + k, o);
+}
+
+// gradient of the pooling: dx [n][h][w][c] = dy [n][h/2][w/2][c] / 4, plus
+// channels ao .. ao + c - 1 of add [n][h][w][ca] (null: nothing), where mask
+// (null: everywhere) is positive; each sum rounded to BF16 as it is formed
+__global__ __launch_bounds__(256) void pool_backward_kernel(const uint16_t* dy, const uint16_t* add, const uint16_t* mask,
+                                                            uint16_t* dx, uint32_t h, uint32_t w, uint32_t c,
+                                                            uint32_t ca, uint32_t ao) {
+    const RowPlace p(h, w, c / 8);
+    if (!p.in) return;
+    const size_t k = (size_t)p.k * 8, q = ((size_t)p.b * h + p.i) * w + p.j;
+    const Vec8 s = load8(dy + (((size_t)p.b * (h / 2) + p.i / 2) * (w / 2) + p.j / 2) * c + k);
+    Vec8 o{v4u{0u, 0u, 0u, 0u}};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o.set(j, 0.25f * s.get(j));
+    if (add) {
+        const Vec8 d = load8(add + q * ca + ao + k);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o.set(j, o.get(j) + d.get(j));
+    }
+    if (mask) o = relu_mask(o, load8(mask + q * c + k));
+    store8(dx + q * c + k, o);
+}
+
+// dst[p][doff + k] (+)= src[p][soff + k] for k < cc; c8 = cc / 8
+__global__ __launch_bounds__(256) void copy_channels8_kernel(const uint16_t* src, uint32_t cs, uint32_t soff, uint16_t* dst,
+                                                             uint32_t cd, uint32_t doff, uint32_t c8, uint32_t items,
+                                                             int32_t accumulate) {
+    for (uint32_t e = blockIdx.x * 256 + threadIdx.x; e < items; e += gridDim.x * 256) {
+        const uint32_t p = e / c8, k = (e - p * c8) * 8;
+        const Vec8 v = load8(src + (size_t)p * cs + soff + k);
+        uint16_t* d = dst + (size_t)p * cd + doff + k;
+        if (!accumulate) {
+            store8(d, v);
+            continue;
+        }
+        Vec8 o = load8(d);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o.set(j, o.get(j) + v.get(j));
+        store8(d, o);
+    }
+}
+
+// eight values per thread, then the rest one by one
+__global__ __launch_bounds__(256) void relu_backward_kernel(const uint16_t* y, const uint16_t* dy, uint16_t* dz,
+                                                            size_t groups, size_t count) {
+    for (size_t e = blockIdx.x * (size_t)256 + threadIdx.x; e < groups; e += (size_t)gridDim.x * 256)
+        store8(dz + e * 8, relu_mask(load8(dy + e * 8), load8(y + e * 8)));
+    for (size_t e = groups * 8 + blockIdx.x * (size_t)256 + threadIdx.x; e < count; e += (size_t)gridDim.x * 256)
         dz[e] = bf2f(y[e]) > 0.0f ? dy[e] : (uint16_t)0;
 }
 
+// the same one value per thread, for channel counts or pointers that rule
+// out 16-byte accesses
 // x [n][h][w][c] -> y [n][h/2][w/2][c], 2x2 means
 __global__ void avgpool2_kernel(const uint16_t* x, uint16_t* y, int32_t n, int32_t h, int32_t w, int32_t c) {
     const size_t total = (size_t)n * (h / 2) * (w / 2) * c;
@@ -674,12 +826,17 @@ __global__ __launch_bounds__(256) void mse_kernel(const uint16_t* y, int32_t cy,
     if (threadIdx.x == 0) partial[blockIdx.x] = lds[0];
 }
 
-__global__ void sum_partials_kernel(const float* partial, int32_t n, float scale, float* out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        float s = 0.0f;
-        for (int32_t i = 0; i < n; ++i) s += partial[i];
-        out[0] = s * scale;
+// out[0] = scale * (sum of the partials), one block, a fixed tree
+__global__ __launch_bounds__(256) void sum_partials_kernel(const float* partial, int32_t n, float scale, float* out) {
+    __shared__ float lds[256];
+    float s = 0.0f;
+    for (int32_t i = threadIdx.x; i < n; i += 256) s += partial[i];
+    lds[threadIdx.x] = s;
+    for (uint32_t o = 128; o > 0; o >>= 1) {
+        __syncthreads();
+        if (threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
     }
+    if (threadIdx.x == 0) out[0] = lds[0] * scale;
 }
 
 // Adam (Kingma & Ba, 2015) on FP32 master weights; also refreshes the

@@ -15,6 +15,8 @@ import numpy as np
 from . import lbm as _lbm
 
 NN_EXPORTS = ["lbm_nn_conv3x3", "lbm_nn_conv3x3_flip", "lbm_nn_conv3x3_wgrad",
+              "lbm_nn_conv3x3_flip_many", "lbm_nn_conv3x3_masked", "lbm_nn_upsample2_concat",
+              "lbm_nn_upsample2_concat_backward", "lbm_nn_avgpool2_backward_add",
               "lbm_nn_relu_backward", "lbm_nn_avgpool2", "lbm_nn_avgpool2_backward",
               "lbm_nn_upsample2", "lbm_nn_upsample2_backward", "lbm_nn_copy_channels",
               "lbm_nn_mse", "lbm_nn_adam", "lbm_nn_to_bf16", "lbm_nn_to_f32",
@@ -32,6 +34,11 @@ def lib():
         L.lbm_nn_conv3x3.argtypes = [P, i32, i32, i32, i32, P, P, i32, i32, P, P]
         L.lbm_nn_conv3x3_flip.argtypes = [P, i32, i32, P, P]
         L.lbm_nn_conv3x3_wgrad.argtypes = [P, P, i32, i32, i32, i32, i32, P, i32, P, P, P]
+        L.lbm_nn_conv3x3_flip_many.argtypes = [i32, C.POINTER(P), C.POINTER(i32), C.POINTER(i32), C.POINTER(P), P]
+        L.lbm_nn_conv3x3_masked.argtypes = [P, i32, i32, i32, i32, P, P, i32, P, P]
+        L.lbm_nn_upsample2_concat.argtypes = [P, i32, i32, i32, i32, P, i32, P, P]
+        L.lbm_nn_upsample2_concat_backward.argtypes = [P, i32, i32, i32, i32, i32, P, P, P]
+        L.lbm_nn_avgpool2_backward_add.argtypes = [P, i32, i32, i32, i32, P, i32, i32, P, P, P]
         L.lbm_nn_relu_backward.argtypes = [P, P, P, i64, P]
         for n in ("lbm_nn_avgpool2", "lbm_nn_avgpool2_backward", "lbm_nn_upsample2",
                   "lbm_nn_upsample2_backward"):
@@ -112,6 +119,24 @@ def conv3x3_wgrad(x, dz, cout, dw, db):
                                       _p(dw), _p(db), _s()))
 
 
+def conv3x3_flip_many(layers):
+    """Flipped weights of several (wt, cin, cout) in one launch."""
+    wfs = [empty_bf16(9, ci, co) for _, ci, co in layers]
+    k = len(layers)
+    _check(lib().lbm_nn_conv3x3_flip_many(
+        k, (C.c_void_p * k)(*[wt.data_ptr() for wt, _, _ in layers]), (C.c_int32 * k)(*[ci for _, ci, _ in layers]),
+        (C.c_int32 * k)(*[co for _, _, co in layers]), (C.c_void_p * k)(*[w.data_ptr() for w in wfs]), _s()))
+    return wfs
+
+
+def conv3x3_masked(x, wt, mask, cout):
+    """conv3x3 without bias and ReLU, zero where mask is not positive."""
+    n, h, w, cin = x.shape
+    y = empty_bf16(n, h, w, cout)
+    _check(lib().lbm_nn_conv3x3_masked(_p(x), n, h, w, cin, _p(wt), _p(mask), cout, _p(y), _s()))
+    return y
+
+
 def relu_backward(y, dy):
     dz = empty_bf16(*y.shape)
     _check(lib().lbm_nn_relu_backward(_p(y), _p(dy), _p(dz), y.numel(), _s()))
@@ -143,6 +168,34 @@ def upsample2_backward(dy):
     n, h2, w2, c = dy.shape
     dx = empty_bf16(n, h2 // 2, w2 // 2, c)
     _check(lib().lbm_nn_upsample2_backward(_p(dy), n, h2 // 2, w2 // 2, c, _p(dx), _s()))
+    return dx
+
+
+def upsample2_concat(x, skip):
+    """concat(upsample2(x), skip) in one pass."""
+    n, h, w, c = x.shape
+    cs = skip.shape[-1]
+    y = empty_bf16(n, 2 * h, 2 * w, c + cs)
+    _check(lib().lbm_nn_upsample2_concat(_p(x), n, h, w, c, _p(skip), cs, _p(y), _s()))
+    return y
+
+
+def upsample2_concat_backward(dcat, y):
+    """Gradient in front of the ReLU whose output y was upsampled into the
+    first channels of a concatenation, from the concatenation's."""
+    n, h, w, c = y.shape
+    dx = empty_bf16(n, h, w, c)
+    _check(lib().lbm_nn_upsample2_concat_backward(_p(dcat), n, h, w, c, dcat.shape[-1], _p(y), _p(dx), _s()))
+    return dx
+
+
+def avgpool2_backward_add(dy, dcat, y):
+    """Gradient in front of the ReLU whose output y was pooled and also
+    concatenated (its last channels), from both gradients."""
+    n, h, w, c = y.shape
+    dx = empty_bf16(n, h, w, c)
+    cd = dcat.shape[-1]
+    _check(lib().lbm_nn_avgpool2_backward_add(_p(dy), n, h, w, c, _p(dcat), cd, cd - c, _p(y), _p(dx), _s()))
     return dx
 
 
@@ -233,7 +286,7 @@ class UNet:
                 h, k = y, k + 1
             skips.append(h)
         for lvl in range(L - 2, -1, -1):
-            h = concat(upsample2(h), skips[lvl])
+            h = upsample2_concat(h, skips[lvl])
             for _ in range(2):
                 lay = self.layers[k]
                 y = conv3x3(h, lay["wbf"], lay["b"], lay["co"], True)
@@ -244,44 +297,34 @@ class UNet:
         tape.append((h, k, None))
         return y, tape
 
-    def _layer_backward(self, h_in, k, dz, need_dx=True):
-        lay = self.layers[k]
-        conv3x3_wgrad(h_in, dz, lay["co"], lay["gw"], lay["gb"])
-        if not need_dx:
-            return None
-        wf = conv3x3_flip(lay["wbf"], lay["ci"], lay["co"])
-        return conv3x3(dz, wf, None, lay["ci"], False)
-
     def backward(self, tape, dy):
         """Fills every layer's gw, gb with the gradient of sum(dy * y)."""
         L = len(self.chans)
-        ti = len(tape) - 1
-        h_in, k, _ = tape[ti]
-        dh = self._layer_backward(h_in, k, dy)
-        ti -= 1
-        dskips = [None] * L
+        flipped = conv3x3_flip_many([(lay["wbf"], lay["ci"], lay["co"]) for lay in self.layers[1:]])
+
+        # one layer: its weight gradient from dz (the gradient in front of its
+        # ReLU), then the gradient of its input, in front of the ReLU that
+        # made the input where there is one (`through`)
+        def layer(dz, through):
+            h_in, k, _ = tape.pop()
+            lay = self.layers[k]
+            conv3x3_wgrad(h_in, dz, lay["co"], lay["gw"], lay["gb"])
+            if k == 0:
+                return None
+            if through:
+                return conv3x3_masked(dz, flipped[k - 1], h_in, lay["ci"])
+            return conv3x3(dz, flipped[k - 1], None, lay["ci"], False)
+
+        tape = list(tape)
+        dz = layer(dy, True)
+        dcats = [None] * L
         for lvl in range(0, L - 1):
-            for _ in range(2):
-                h_in, k, y = tape[ti]
-                dh = self._layer_backward(h_in, k, relu_backward(y, dh))
-                ti -= 1
-            up_ch = dh.shape[-1] - self.chans[lvl]
-            dskip = empty_bf16(*dh.shape[:-1], self.chans[lvl])
-            copy_channels(dh, up_ch, dskip, 0, self.chans[lvl])
-            dup = empty_bf16(*dh.shape[:-1], up_ch)
-            copy_channels(dh, 0, dup, 0, up_ch)
-            dskips[lvl] = dskip
-            dh = upsample2_backward(dup)
+            dcats[lvl] = layer(layer(dz, True), False)
+            dz = upsample2_concat_backward(dcats[lvl], tape[-1][2])
         for lvl in range(L - 1, -1, -1):
-            if lvl < L - 1:
-                copy_channels(dskips[lvl], 0, dh, 0, dh.shape[-1], accumulate=True)
-            for j in range(2):
-                h_in, k, y = tape[ti]
-                last = lvl == 0 and j == 1
-                dh = self._layer_backward(h_in, k, relu_backward(y, dh), need_dx=not last)
-                ti -= 1
+            dh = layer(layer(dz, True), False)
             if lvl > 0:
-                dh = avgpool2_backward(dh)
+                dz = avgpool2_backward_add(dh, dcats[lvl - 1], tape[-1][2])
 
     def adam(self, lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8):
         self.steps += 1

@@ -64,3 +64,73 @@ def test_conv3x3_wgrad_tiles(n, h, w, ci, co, chunks):
         assert np.all(np.abs(got - ref) <= 1e-5 * scale + 1e-6)
         if with_bias:
             assert np.all(np.abs(db.cpu().numpy() - bref) <= 1e-5 * bscale + 1e-6)
+
+
+@pytest.mark.parametrize("n,h,w,c,cs", [(1, 1, 1, 8, 8), (2, 5, 3, 16, 24), (3, 17, 33, 64, 32), (1, 2, 300, 72, 8)])
+def test_joins_equal_their_parts(n, h, w, c, cs):
+    """The one-pass joins against the single layers they combine, bit for bit,
+    and those against numpy (exact but for the stated roundings)."""
+    import torch
+    from paper_2211_03160_amd import nn
+    rng = np.random.default_rng(c + cs)
+    x, dlow = (_bf(rng.standard_normal((n, h, w, c))) for _ in range(2))
+    skip, big = (_bf(rng.standard_normal((n, 2 * h, 2 * w, k))) for k in (cs, c + cs))
+    xd, skd, bigd, dlowd = _dev_bf16(x), _dev_bf16(skip), _dev_bf16(big), _dev_bf16(dlow)
+    # upsample beside skip
+    y = nn.upsample2_concat(xd, skd)
+    assert torch.equal(y, nn.concat(nn.upsample2(xd), skd))
+    assert np.array_equal(_host(y), np.concatenate([R.upsample2(x), skip], -1))
+    # its gradient in front of the ReLU
+    part = nn.empty_bf16(n, 2 * h, 2 * w, c)
+    nn.copy_channels(bigd, 0, part, 0, c)
+    assert np.array_equal(_host(part), big[..., :c])
+    assert torch.equal(nn.upsample2_concat_backward(bigd, xd), nn.relu_backward(xd, nn.upsample2_backward(part)))
+    # pooling gradient plus the last channels of the concatenation's
+    yhigh = _dev_bf16(_bf(rng.standard_normal((n, 2 * h, 2 * w, c))))
+    want = nn.avgpool2_backward(dlowd)
+    assert np.array_equal(_host(want), R.avgpool2_backward(dlow))  # a quarter of a BF16 value is exact
+    nn.copy_channels(bigd, cs, want, 0, c, accumulate=True)
+    assert torch.equal(nn.avgpool2_backward_add(dlowd, bigd, yhigh), nn.relu_backward(yhigh, want))
+    assert np.array_equal(_host(nn.avgpool2(bigd)), _bf(R.avgpool2(big)))
+
+
+def test_layers_without_16_byte_access():
+    """Channel counts that are no multiple of 8 and tensors off 16-byte
+    addresses take the element kernels: the same values."""
+    import torch
+    from paper_2211_03160_amd import nn
+    rng = np.random.default_rng(1)
+    x = _bf(rng.standard_normal((2, 4, 6, 12)))
+    xd = _dev_bf16(x)
+    up = nn.upsample2(xd)
+    assert np.array_equal(_host(up), R.upsample2(x))
+    assert np.array_equal(_host(nn.avgpool2(xd)), _bf(R.avgpool2(x)))
+    assert np.array_equal(_host(nn.avgpool2_backward(xd)), R.avgpool2_backward(x))
+    assert np.allclose(_host(nn.upsample2_backward(xd)), R.upsample2_backward(x), rtol=BF, atol=0)
+    flat = torch.zeros(1 + x.size, dtype=torch.int16, device="cuda")
+    flat[1:] = xd.flatten()
+    off = flat[1:]  # two bytes off
+    dy = _dev_bf16(rng.standard_normal(x.size))
+    assert torch.equal(nn.relu_backward(off, dy), nn.relu_backward(xd.flatten(), dy))
+    with pytest.raises(Exception, match="bad arguments"):
+        nn.upsample2_concat(xd, up)
+    with pytest.raises(Exception, match="bad arguments"):
+        nn.upsample2_concat_backward(up, xd)
+
+
+@pytest.mark.parametrize("ci,co", [(32, 64), (48, 32), (16, 16)])
+def test_masked_convolution_and_flips(ci, co):
+    """The masked data gradient equals the convolution followed by the ReLU's
+    gradient, and flipped weights of many layers equal those of each."""
+    import torch
+    from paper_2211_03160_amd import nn
+    rng = np.random.default_rng(ci)
+    dz = _dev_bf16(rng.standard_normal((2, 9, 11, ci)))
+    mask = _dev_bf16(rng.standard_normal((2, 9, 11, co)))
+    wt = _dev_bf16(rng.standard_normal((9, co, ci)) * 0.2)
+    assert torch.equal(nn.conv3x3_masked(dz, wt, mask, co),
+                       nn.relu_backward(mask, nn.conv3x3(dz, wt, None, co, False)))
+    layers = [(_dev_bf16(rng.standard_normal((9, o, i))), i, o) for i, o in [(16, 48), (ci, co), (96, 32)] * 13]
+    for (w, i, o), wf in zip(layers, nn.conv3x3_flip_many(layers)):
+        assert torch.equal(wf, w.flip(0).transpose(1, 2).contiguous())
+        assert torch.equal(wf, nn.conv3x3_flip(w, i, o))
