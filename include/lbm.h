@@ -351,8 +351,11 @@ lbm_status lbm_batch_init_fields(lbm_batch* b, int32_t k, const double* rho, con
                                  const double* T);
 
 /* Enqueues n steps of every cavity (graph replays when configured, then
- * launches of lbm_batch_get_steps_per_launch steps, then one-step launches
- * for the remainder).  Asynchronous.                                    */
+ * launches of several steps, then one-step launches for the remainder).  A
+ * 2D batch of at most 9 to 15 million nodes (any number with FP64 storage)
+ * takes 4 or 5 steps per launch through LDS tiles until a count or a
+ * streaming shape is set; else launches take
+ * lbm_batch_get_steps_per_launch steps.  Asynchronous.                  */
 lbm_status lbm_batch_step(lbm_batch* b, int64_t n);
 
 /* Steps per launch of lbm_batch_step: 1 (batch_step_kernel, the shape of
@@ -390,7 +393,10 @@ lbm_status lbm_batch_unstable(lbm_batch* b, int32_t* flags);
  * and 4 steps per launch (FP32: 2 to 5; FP64: 2) x segment rows
  * 16/24/32/48/64 x 2/4/8 wavefronts per block.  The winner sets the configuration and the steps
  * per launch (graph_steps is left as configured); results do not depend on
- * any of them (bitwise).  The timing steps are real steps: t advances by
+ * any of them (bitwise).  Where the batch can run through LDS tiles
+ * (lbm_batch_step), those launches are timed too, without advancing t and
+ * without an entry in ms_per_step, and stay in use if they are faster than
+ * every candidate.  The timing steps are real steps: t advances by
  * (steps + 1) x the steps per launch of every candidate.  ms_per_step
  * (nullable) receives up to LBM_BATCH_TUNE_MAX timings in candidate order,
  * ncand their number.                                                   */

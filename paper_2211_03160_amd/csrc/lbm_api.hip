@@ -682,6 +682,10 @@ template <class St> constexpr uint32_t tile2_most_nodes() {
     return bf16 || !same ? 15000000u : 9000000u;
 }
 
+// steps per launch on 32 x 16 and on 32 x 32 regions
+template <class St> constexpr int tile2_mid_steps() { return sizeof(typename St::R) == 8 ? 4 : 5; }
+template <class St> constexpr int tile2_big_steps() { return sizeof(typename St::TF) == 4 ? 5 : 4; }
+
 // n steps of a 2D cavity whose steps per launch were not set: through the
 // tile kernel where it is the fastest; returns the steps left over.
 //
@@ -702,7 +706,7 @@ template <class St> int64_t tile2_auto(lbm_ctx* c, int64_t n) {
     const uint32_t nx = c->geo.nx, ny = c->geo.ny;
     if (c->geo.N > tile2_most_nodes<St>() || (ny < 24 && c->geo.N > 65536u)) return n;
     constexpr bool f64 = sizeof(typename St::R) == 8;
-    constexpr int kMid = f64 ? 4 : 5, kBig = sizeof(typename St::TF) == 4 ? 5 : 4;
+    constexpr int kMid = tile2_mid_steps<St>(), kBig = tile2_big_steps<St>();
     auto tiles = [&](uint32_t ox, uint32_t oy) { return (uint64_t)((nx + ox - 1) / ox) * ((ny + oy - 1) / oy); };
     const uint64_t cus = (uint64_t)std::max(c->cus, 1);
     if (tiles(8, 8) <= 2 * cus) return tile2_run<St, 16, 16, 0>(c, n, 5);

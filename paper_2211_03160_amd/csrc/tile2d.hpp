@@ -81,9 +81,13 @@ struct TileFlux {
     }
 };
 
-// one block's K steps, with (Walls) or without wall rules
-template <class St, int RX, int RY, int KT, bool Walls>
-__device__ __forceinline__ void tile2_steps(const Tile2Args<St>& a, typename St::R* lds, int32_t x0, int32_t y0) {
+// One block's K steps, with (Walls) or without wall rules, from the state of
+// parity tp.  With Report, returns false on a thread that computed, at any
+// step, a node of the domain from valid sources whose new rho or T is not
+// finite or whose speed exceeds the lattice sound speed.
+template <class St, int RX, int RY, int KT, bool Walls, bool Report>
+__device__ __forceinline__ bool tile2_steps(const Tile2Args<St>& a, typename St::R* lds, int32_t x0, int32_t y0,
+                                            int32_t tp) {
     using R = typename St::R;
     using L = Flow<2>;
     using H = Heat<2>;
@@ -107,9 +111,17 @@ __device__ __forceinline__ void tile2_steps(const Tile2Args<St>& a, typename St:
     R* mine = lds + (RX + 1) + threadIdx.x;  // a margin takes the edge threads' reads
     R f[QF], h[QG];
     // a slot keeps the last step of its parity: only steps K - 1 and K write
-    auto flux = [&](int j) { return TileFlux{a.flux + a.slot[(a.t_parity + j) & 1], own && j >= K - 1}; };
-    step_node<2, St, Walls>(g, a.c, nb, x, y, 0u, global_src<St, QF, QG>(g, nb, a.fsrc, a.gsrc, idx),
-                            TileDst<St, N>{mine, f, h}, flux(1));
+    auto flux = [&](int j) { return TileFlux{a.flux + a.slot[(tp + j) & 1], own && j >= K - 1}; };
+    // the last step at which this thread's node is valid (0: none)
+    const int edge = min(min(tx, RX - 1 - tx), min(ty, RY - 1 - ty));
+    const int valid = Report && rx >= 0 && ry >= 0 ? edge + 1 : 0;
+    bool bad = false;
+    {
+        const bool ok = step_node<2, St, Walls>(g, a.c, nb, x, y, 0u,
+                                                global_src<St, QF, QG>(g, nb, a.fsrc, a.gsrc, idx),
+                                                TileDst<St, N>{mine, f, h}, flux(1));
+        if constexpr (Report) bad = !ok && valid >= 1;
+    }
     auto middle = [&](const int j) __attribute__((always_inline)) {
         const bool need = wy1 >= j - 1 && wy0 <= RY - j;
         R pf[QF], pg[QG];  // the pull of step j, read before any thread overwrites step j - 1
@@ -130,9 +142,11 @@ __device__ __forceinline__ void tile2_steps(const Tile2Args<St>& a, typename St:
             });
         }
         __syncthreads();
-        if (need)
-            step_node<2, St, Walls>(g, a.c, nb, x, y, 0u, PreSrc<St, QF, QG>{pf, pg}, TileDst<St, N>{mine, f, h},
-                                    flux(j));
+        if (need) {
+            const bool ok = step_node<2, St, Walls>(g, a.c, nb, x, y, 0u, PreSrc<St, QF, QG>{pf, pg},
+                                                    TileDst<St, N>{mine, f, h}, flux(j));
+            if constexpr (Report) bad = bad || (!ok && valid >= j);
+        }
     };
     if constexpr (KT > 0) {
         static_for<2, KT>([&](auto jc) { middle(decltype(jc)::value); });
@@ -140,26 +154,59 @@ __device__ __forceinline__ void tile2_steps(const Tile2Args<St>& a, typename St:
         for (int j = 2; j < K; ++j) middle(j);
     }
     __syncthreads();
-    if (own)
-        step_node<2, St, Walls>(g, a.c, nb, x, y, 0u, TileSrc<St, N, RX>{mine, f, h},
-                                GlobalDst<St, QF, QG, false, false>(a.fdst, a.gdst, idx), flux(K));
+    if (own) {
+        const bool ok = step_node<2, St, Walls>(g, a.c, nb, x, y, 0u, TileSrc<St, N, RX>{mine, f, h},
+                                                GlobalDst<St, QF, QG, false, false>(a.fdst, a.gdst, idx), flux(K));
+        if constexpr (Report) bad = bad || !ok;
+    }
+    return !bad;
 }
 
-template <class St, int RX, int RY, int KT>
-__global__ __launch_bounds__(RX* RY)
-void tile2_kernel(Tile2Args<St> a) {
-    __shared__ typename St::R lds[12 * RX * RY + 2 * (RX + 1)];
-    const uint32_t blk = logical_block(a.blocks_per_xcd);
-    if (blk >= a.tiles) return;  // whole block
+// tile `tile` of a
+template <class St, int RX, int RY, int KT, bool Report>
+__device__ __forceinline__ bool tile2_tile(const Tile2Args<St>& a, typename St::R* lds, uint32_t tile, int32_t tp) {
     const Geometry& g = a.geo;
     const int32_t halo = (KT > 0 ? KT : a.steps) - 1;
-    const int32_t x0 = (int32_t)(blk % a.tiles_x) * (RX - 2 * halo) - halo;
-    const int32_t y0 = (int32_t)(blk / a.tiles_x) * (RY - 2 * halo) - halo;
+    const int32_t x0 = (int32_t)(tile % a.tiles_x) * (RX - 2 * halo) - halo;
+    const int32_t y0 = (int32_t)(tile / a.tiles_x) * (RY - 2 * halo) - halo;
     // a region that stays one node clear of every wall runs without wall rules
     const bool inner_x = g.periodic[0] || (x0 >= 1 && x0 + RX - 1 <= (int32_t)g.nx - 2);
     const bool inner_y = g.periodic[1] || (y0 >= 1 && y0 + RY - 1 <= (int32_t)g.ny - 2);
-    if (inner_x && inner_y) tile2_steps<St, RX, RY, KT, false>(a, lds, x0, y0);
-    else tile2_steps<St, RX, RY, KT, true>(a, lds, x0, y0);
+    if (inner_x && inner_y) return tile2_steps<St, RX, RY, KT, false, Report>(a, lds, x0, y0, tp);
+    return tile2_steps<St, RX, RY, KT, true, Report>(a, lds, x0, y0, tp);
+}
+
+template <int RX, int RY> constexpr int tile2_lds() { return 12 * RX * RY + 2 * (RX + 1); }
+
+template <class St, int RX, int RY, int KT> __global__ __launch_bounds__(RX* RY) void tile2_kernel(Tile2Args<St> a) {
+    __shared__ typename St::R lds[tile2_lds<RX, RY>()];
+    const uint32_t blk = logical_block(a.blocks_per_xcd);
+    if (blk >= a.tiles) return;  // whole block
+    tile2_tile<St, RX, RY, KT, false>(a, lds, blk, a.t_parity);
+}
+
+// Many 2D cavities: block b takes tile b of the concatenated tiles of all
+// cavities, which tile_cavity maps to its cavity.
+template <class St> struct BatchTile2Args {
+    const Tile2Args<St>* desc;    // [2][count]: the cavities' arguments with buffer A, B as source
+    const uint16_t* tile_cavity;  // [tiles]
+    const uint32_t* tile0;        // [count] first tile of each cavity
+    uint32_t tiles, count, blocks_per_xcd;
+    int32_t src;                  // source buffer of this launch
+    int32_t t_parity;             // (t of the input state) mod 2
+    int32_t* unstable;            // per-cavity flag, set on a non-finite node
+};
+
+template <class St, int RX, int RY, int KT>
+__global__ __launch_bounds__(RX* RY) void batch_tile2_kernel(BatchTile2Args<St> b) {
+    __shared__ typename St::R lds[tile2_lds<RX, RY>()];
+    const uint32_t blk = logical_block(b.blocks_per_xcd);
+    if (blk >= b.tiles) return;  // whole block
+    const uint32_t k = b.tile_cavity[blk];
+    // through the constant address space, like the streaming kernel's
+    using CArgs = const __attribute__((address_space(4))) Tile2Args<St>;
+    const Tile2Args<St>& a = *(const Tile2Args<St>*)((CArgs*)b.desc + ((uint32_t)b.src * b.count + k));
+    if (!tile2_tile<St, RX, RY, KT, true>(a, lds, blk - b.tile0[k], b.t_parity)) b.unstable[k] = 1;
 }
 
 }  // namespace lbm

@@ -47,3 +47,72 @@ def test_default_launches_bitwise(storage, shape):
                 x, y = np.frombuffer(one, np.uint8), np.frombuffer(got, np.uint8)
                 bad = np.flatnonzero(x != y)
                 pytest.fail(f"{name} {shape} {storage} {steps}: {bad.size} bytes differ, first at {bad[:8]}")
+
+
+def _batch_cfgs(storage, kind):
+    """Batches that take each region shape (16 x 16, 32 x 16, 32 x 32; FP64
+    the first two), ragged and with every boundary kind."""
+    rb = lambda n, **k: W.rayleigh_benard(2, n, ra=5e4, pr=0.71, storage=storage, **k)  # noqa: E731
+    if kind == "small":
+        return [rb((33, 17)), W.side_heated(2, (41, 41), ra=1e6, storage=storage), rb((66, 33), lateral="periodic"),
+                rb((3, 2)), rb((130, 57))]
+    if kind == "mid":
+        return [rb((129, 129)), rb((193, 97)), W.side_heated(2, (65, 66), ra=1e5, storage=storage),
+                rb((200, 200), lateral="periodic")]
+    return [rb((257, 257)), rb((513, 257)), W.side_heated(2, (300, 127), ra=1e5, storage=storage)]
+
+
+@pytest.mark.parametrize("storage", ["fp32", "fp64", "fp16", "bf16", "mixed"])
+@pytest.mark.parametrize("kind", ["small", "mid", "big"])
+def test_batch_tile_launches_equal_single_steps(storage, kind):
+    """The default launches of a batch (and their graph replay, checked after
+    each) against the same batch in single steps: fields, wall fluxes and
+    Nusselt numbers bit for bit."""
+    cfgs = _batch_cfgs(storage, kind)
+    seeds = [3 + k for k in range(len(cfgs))]
+    one, default, graph = (lbm.Batch(cfgs) for _ in range(3))
+    one.steps_per_launch = 1
+    graph.set_config(graph_steps=14)
+    for b in (one, default, graph):
+        b.init(seeds, [2e-2] * len(cfgs))
+    for n in (5, 14, 3, 28):
+        for b in (one, default, graph):
+            b.step(n)
+        assert not default.unstable().any()
+        for k in range(len(cfgs)):
+            ref = one.cavity(k).fields()
+            for b in (default, graph):
+                got = b.cavity(k)
+                assert all(np.array_equal(x, y) for x, y in zip(ref, got.fields())), (n, k)
+                assert np.array_equal(one.cavity(k).wall_flux(), got.wall_flux()), (n, k)
+        assert np.array_equal(np.nan_to_num(one.nusselt()), np.nan_to_num(default.nusselt()))
+
+
+def test_batch_tiles_flag_a_diverging_member_only():
+    cfgs = [W.rayleigh_benard(2, (65, 65), ra=1e5, pr=0.71, storage="fp32") for _ in range(3)]
+    b = lbm.Batch(cfgs)
+    b.init([1, 2, 3], [1e-3] * 3)
+    n = 65 * 65
+    u = np.zeros((2, n))
+    u[0, n // 2] = 0.9  # faster than the lattice sound speed
+    b.init_fields(1, None, u, np.full(n, 0.5))
+    b.step(5)
+    assert b.unstable().tolist() == [False, True, False]
+
+
+def test_autotuner_leaves_wall_flux_and_state_to_its_steps():
+    """The tile launches the autotuner times do not advance the batch: after
+    tuning, state and Nusselt numbers are those of t single steps."""
+    cfgs = _batch_cfgs("fp32", "mid")
+    a, b = lbm.Batch(cfgs), lbm.Batch(cfgs)
+    b.steps_per_launch = 1
+    for x in (a, b):
+        x.init([1] * len(cfgs), [1e-2] * len(cfgs))
+    a.tune(steps=1)
+    b.step(a.t)
+    for extra in (0, 7):
+        a.step(extra)
+        b.step(extra)
+        assert np.array_equal(a.nusselt(), b.nusselt())
+        for k in range(len(cfgs)):
+            assert all(np.array_equal(x, y) for x, y in zip(a.cavity(k).fields(), b.cavity(k).fields()))
