@@ -718,6 +718,14 @@ template <class St> int64_t tile2_auto(lbm_ctx* c, int64_t n) {
     }
 }
 
+// Whether the 3D two-step kernel is used where the caller chose no count.
+// Small grids stay in the caches, and the two-step kernel's blocks (one tile
+// of columns each, a plane at a time) leave compute units idle, so the
+// one-step kernel wins there.  us per step in FP32, one step against two:
+// 17^3 4.0 / 6.1, 33^3 4.4 / 6.5, 49^3 5.9 / 9.1, 65^3 13.7 / 13.3, 97^3 37 /
+// 27.7.
+bool stream3_pays(const lbm_ctx* c) { return c->geo.N >= 250000u; }
+
 // z segments of the 3D two-step kernel.  Each segment repeats the first
 // step on one plane below and one above it, and its block holds a compute
 // unit's LDS for the whole segment, so a launch runs in rounds: each XCD
@@ -979,7 +987,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
         } else if constexpr (sizeof(typename St::R) == 4) {
             // 3D: two steps per launch through the LDS plane ring (FP64's
             // ring would not fit the LDS)
-            if (c->steps_per_launch == 2 && n >= 2 && streamable3(c)) {
+            if (c->steps_per_launch == 2 && n >= 2 && streamable3(c) && (c->steps_set || stream3_pays(c))) {
                 stream3_launches<St>(c, n / 2);
                 n -= n / 2 * 2;
             }
