@@ -100,6 +100,16 @@ lbm_status lbm_nn_avgpool2_backward_add(const uint16_t* dy, int32_t n, int32_t h
                                         int32_t c, const uint16_t* add, int32_t ca, int32_t aoff,
                                         const uint16_t* mask, uint16_t* dx, void* stream);
 
+/* Forward pass of a U-Net in one call (a host loop over the calls above):
+ * per level two conv3x3 + ReLU, below the first one after avgpool2; then per
+ * level upwards upsample2_concat with that level's output and two conv3x3 +
+ * ReLU; a last conv3x3.  Host arrays: cout, wt, bias of the 4 levels - 1
+ * convolutions, and out, where each of the 6 levels - 3 results goes, in this
+ * order.                                                                */
+lbm_status lbm_nn_unet_forward(int32_t levels, const uint16_t* x, int32_t n, int32_t h, int32_t w,
+                               int32_t cin, const int32_t* cout, const uint16_t* const* wt,
+                               const float* const* bias, uint16_t* const* out, void* stream);
+
 /* Channel slice copy for concatenation and its gradient:
  * dst[p][doff + k] = src[p][soff + k] (or += when accumulate != 0), k < cc,
  * p < pixels; cs, cd are the channel counts of src and dst.              */

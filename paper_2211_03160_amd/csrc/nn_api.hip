@@ -317,6 +317,42 @@ lbm_status lbm_nn_upsample2_concat_backward(const uint16_t* dy, int32_t n, int32
     return launched("upsample2_concat_backward");
 }
 
+lbm_status lbm_nn_unet_forward(int32_t levels, const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cin,
+                               const int32_t* cout, const uint16_t* const* wt, const float* const* bias,
+                               uint16_t* const* out, void* stream) {
+    constexpr int32_t kMost = 32;
+    if (!cout || !wt || !bias || !out || levels < 1 || levels > kMost)
+        return nn_fail(LBM_E_INVALID, "unet_forward: bad arguments");
+    const uint16_t* skip[kMost];
+    int32_t skip_c[kMost], k = 0;
+    const uint16_t* t = x;
+    auto conv = [&](int32_t relu) {
+        const lbm_status st = conv3x3(t, n, h, w, cin, wt[k], bias[k], nullptr, cout[k], relu, *out, stream);
+        t = *out++;
+        cin = cout[k++];
+        return st;
+    };
+    lbm_status st = LBM_OK;
+    for (int32_t l = 0; l < levels && !st; ++l) {
+        if (l) {
+            st = lbm_nn_avgpool2(t, n, h, w, cin, *out, stream);
+            t = *out++;
+            h /= 2, w /= 2;
+        }
+        if (!st) st = conv(1);
+        if (!st) st = conv(1);
+        skip[l] = t, skip_c[l] = cin;
+    }
+    for (int32_t l = levels - 2; l >= 0 && !st; --l) {
+        st = lbm_nn_upsample2_concat(t, n, h, w, cin, skip[l], skip_c[l], *out, stream);
+        t = *out++;
+        h *= 2, w *= 2, cin += skip_c[l];
+        if (!st) st = conv(1);
+        if (!st) st = conv(1);
+    }
+    return st ? st : conv(0);
+}
+
 lbm_status lbm_nn_copy_channels(const uint16_t* src, int32_t cs, int32_t soff, uint16_t* dst, int32_t cd,
                                 int32_t doff, int32_t cc, int64_t pixels, int32_t accumulate, void* stream) {
     if (!src || !dst || !pos(cs) || !pos(cd) || !pos(cc) || soff < 0 || doff < 0 || soff + cc > cs ||

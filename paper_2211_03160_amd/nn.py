@@ -16,7 +16,7 @@ from . import lbm as _lbm
 
 NN_EXPORTS = ["lbm_nn_conv3x3", "lbm_nn_conv3x3_flip", "lbm_nn_conv3x3_wgrad",
               "lbm_nn_conv3x3_flip_many", "lbm_nn_conv3x3_masked", "lbm_nn_upsample2_concat",
-              "lbm_nn_upsample2_concat_backward", "lbm_nn_avgpool2_backward_add",
+              "lbm_nn_upsample2_concat_backward", "lbm_nn_avgpool2_backward_add", "lbm_nn_unet_forward",
               "lbm_nn_relu_backward", "lbm_nn_avgpool2", "lbm_nn_avgpool2_backward",
               "lbm_nn_upsample2", "lbm_nn_upsample2_backward", "lbm_nn_copy_channels",
               "lbm_nn_mse", "lbm_nn_adam", "lbm_nn_to_bf16", "lbm_nn_to_f32",
@@ -39,6 +39,8 @@ def lib():
         L.lbm_nn_upsample2_concat.argtypes = [P, i32, i32, i32, i32, P, i32, P, P]
         L.lbm_nn_upsample2_concat_backward.argtypes = [P, i32, i32, i32, i32, i32, P, P, P]
         L.lbm_nn_avgpool2_backward_add.argtypes = [P, i32, i32, i32, i32, P, i32, i32, P, P, P]
+        L.lbm_nn_unet_forward.argtypes = [i32, P, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(P), C.POINTER(P),
+                                          C.POINTER(P), P]
         L.lbm_nn_relu_backward.argtypes = [P, P, P, i64, P]
         for n in ("lbm_nn_avgpool2", "lbm_nn_avgpool2_backward", "lbm_nn_upsample2",
                   "lbm_nn_upsample2_backward"):
@@ -271,30 +273,43 @@ class UNet:
     def forward(self, x):
         """x: BF16 [n, h, w, cin] (h, w divisible by 2^(levels-1)).
         Returns (y, tape)."""
-        tape = []
-        k = 0
-        skips = []
-        h = x
-        L = len(self.chans)
-        for lvl in range(L):
-            if lvl > 0:
-                h = avgpool2(h)
-            for _ in range(2):
-                lay = self.layers[k]
-                y = conv3x3(h, lay["wbf"], lay["b"], lay["co"], True)
-                tape.append((h, k, y))
-                h, k = y, k + 1
-            skips.append(h)
-        for lvl in range(L - 2, -1, -1):
-            h = upsample2_concat(h, skips[lvl])
-            for _ in range(2):
-                lay = self.layers[k]
-                y = conv3x3(h, lay["wbf"], lay["b"], lay["co"], True)
-                tape.append((h, k, y))
-                h, k = y, k + 1
-        lay = self.layers[k]
-        y = conv3x3(h, lay["wbf"], lay["b"], lay["co"], False)
-        tape.append((h, k, None))
+        # One buffer for what stays between the layers and one call that
+        # launches them all, before the views of the tape are made: the host
+        # is then ahead of the GPU.  Two levels on 8 x 34 x 34 pixels: 97 us
+        # with a call and an allocation per layer, of which 60 on the GPU.
+        import torch
+        n, h, w, c = x.shape
+        L, layers = len(self.chans), self.layers
+        co = [lay["co"] for lay in layers]
+        shapes, k = [], 0  # of every result, in launch order
+        for lvl in list(range(L)) + list(range(L - 2, -1, -1)):
+            if k >= 2 * L:
+                h, w, c = 2 * h, 2 * w, c + co[2 * lvl + 1]
+                shapes.append((n, h, w, c))
+            elif lvl > 0:
+                h, w = h // 2, w // 2
+                shapes.append((n, h, w, c))
+            c = co[k + 1]
+            shapes += [(n, h, w, co[k]), (n, h, w, c)]
+            k += 2
+        off = [0]
+        for s in shapes:
+            off.append(off[-1] + s[0] * s[1] * s[2] * s[3])
+        held = torch.empty(off[-1], dtype=torch.int16, device="cuda")
+        y = empty_bf16(n, h, w, co[k])
+        m, P = len(layers), C.c_void_p
+        base = held.data_ptr()
+        _check(lib().lbm_nn_unet_forward(
+            L, _p(x), *x.shape, (C.c_int32 * m)(*co), (P * m)(*[lay["wbf"].data_ptr() for lay in layers]),
+            (P * m)(*[lay["b"].data_ptr() for lay in layers]),
+            (P * len(off))(*[base + 2 * o for o in off[:-1]], y.data_ptr()), _s()))
+        tape, t = [], x
+        for i, s in enumerate(shapes):
+            r = held.as_strided(s, (s[1] * s[2] * s[3], s[2] * s[3], s[3], 1), off[i])
+            if i < 2 or (i - 2) % 3:
+                tape.append((t, len(tape), r))
+            t = r
+        tape.append((t, k, None))
         return y, tape
 
     def backward(self, tape, dy):
