@@ -327,7 +327,7 @@ typedef struct lbm_batch_config {
     int32_t reserved;    /* 0                                                 */
     int32_t stream_rows;  /* rows per strip segment of the streaming kernel
                              (several steps per launch), 8 .. 256; 0: the
-                             single-cavity default of the storage mode        */
+                             default of the storage mode                      */
     int32_t stream_waves; /* wavefronts per block of the streaming kernel:
                              1, 2, 4 or 8; 0: 4                               */
 } lbm_batch_config;

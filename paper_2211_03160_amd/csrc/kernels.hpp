@@ -905,8 +905,9 @@ template <class St> struct StreamArgs {
     int32_t t_parity;                 // (t of the input state) mod 2: step j writes slot (t + j) mod 2
     Geometry geo;
     Coef<typename St::R> c;
-    uint32_t strips;          // strips across x
+    uint32_t strips, segs;    // strips across x, row segments of a strip
     uint32_t seg_rows;        // rows per strip segment
+    uint32_t first_rows;      // rows of the first one
     uint32_t units;           // strips x segments, one per wavefront
     uint32_t blocks_per_xcd;
 };
@@ -925,12 +926,41 @@ template <class St, int NS> constexpr int stream_waves_per_simd() {
     else return LBM_STREAM_WAVES_PER_SIMD;
 }
 
-// One wavefront's work unit (strip unit % strips, row segment unit /
-// strips) of a, advancing NS steps from the state of parity tp.  With
-// Report, returns false on a lane that computed, at any of the NS steps, a
-// real node whose new rho or T is not finite or whose speed exceeds the
-// lattice sound speed.
-template <class St, bool O32, int NS, int D, bool Report>
+// Whether a block's wavefronts wait for each other every few rows (a
+// wavefront that has ended no longer takes part).  It keeps neighbouring
+// strips on the same rows, so that the two parts of a memory line that they
+// share are stored close together and merge in the L2; drifting apart, 7 % of
+// the write requests were of partial lines (8192^2 periodic box, FP32, five
+// steps, 64 rows: 2069 us a launch, 1818 in step).  8193^2 with walls, GLUPS
+// at the best segment length without and with: FP32 at five steps 171 / 179;
+// 16-bit storage, which writes half as much, loses: FP16 at three 181 / 175,
+// BF16 at four 195 / 179, FP16-f+FP32-g at four 178 / 167.
+template <class St, int NS> constexpr bool stream_in_step() {
+    return std::is_same_v<St, StF32> && NS == 5;
+}
+
+// The strip and the row segment of a work unit.  Units follow the segments,
+// strip by strip, except that the two strips at walls in x come first in
+// each group of kUnitGroup segments: wall rules make a strip's sweep 1.6 times
+// as long, and so the wavefronts of a block, and what a launch ends on, take
+// alike time.  A group, not the whole grid: every XCD then has its share.
+constexpr uint32_t kUnitGroup = 16;
+struct UnitPos {
+    uint32_t strip, seg;
+};
+__device__ __forceinline__ UnitPos unit_pos(uint32_t unit, uint32_t strips, uint32_t segs, bool walls_x) {
+    if (!walls_x || strips < 3) return {unit % strips, unit / strips};
+    const uint32_t seg0 = unit / (strips * kUnitGroup) * kUnitGroup;
+    const uint32_t here = min(kUnitGroup, segs - seg0), r = unit - seg0 * strips;
+    if (r < 2 * here) return {r < here ? 0u : strips - 1, seg0 + (r < here ? r : r - here)};
+    return {1 + (r - 2 * here) % (strips - 2), seg0 + (r - 2 * here) / (strips - 2)};
+}
+
+// One wavefront's work unit of a, advancing NS steps from the state of
+// parity tp.  With Report, returns false on a lane that computed, at any of
+// the NS steps, a real node whose new rho or T is not finite or whose speed
+// exceeds the lattice sound speed.  InStep: see stream_in_step.
+template <class St, bool O32, int NS, int D, bool Report, bool InStep>
 __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t unit, int32_t tp) {
     using R = typename St::R;
     constexpr int QF = Flow<2>::Q, QG = Heat<2>::Q;
@@ -939,9 +969,10 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
     const Geometry& g = a.geo;
     const int lane = (int)(threadIdx.x & 63);
     bool bad = false;
-    const int32_t x0 = (int32_t)((unit % a.strips) * W);
-    const int32_t y0 = (int32_t)((unit / a.strips) * a.seg_rows);
-    const int32_t rows = min((int32_t)a.seg_rows, (int32_t)g.ny - y0);
+    const UnitPos at = unit_pos(unit, a.strips, a.segs, !g.periodic[0]);
+    const int32_t x0 = (int32_t)(at.strip * W);
+    const int32_t y0 = at.seg ? (int32_t)(a.first_rows + (at.seg - 1) * a.seg_rows) : 0;
+    const int32_t rows = min((int32_t)(at.seg ? a.seg_rows : a.first_rows), (int32_t)g.ny - y0);
     const int32_t cx = x0 - NS + lane;                          // this lane's column, unwrapped
     const int32_t col = region_coord(cx, g.nx, g.periodic[0]);  // -1 beyond a wall
     const uint32_t ucol = col < 0 ? 0u : (uint32_t)col;         // any in-domain column for dead lanes
@@ -1094,6 +1125,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
     // count is rounded up to whole groups of U (the extra ones store nothing)
     auto sweep = [&](auto walls) {
         for (int32_t k = 0; k < rows + 3 * NS - 1 + D; k += U) {
+            if constexpr (InStep) __builtin_amdgcn_s_barrier();
             static_for<0, U>([&](auto sc) { iteration(sc, walls, k + decltype(sc)::value); });
         }
     };
@@ -1117,7 +1149,7 @@ void stream_kernel(StreamArgs<St> a) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t unit = logical_block(a.blocks_per_xcd) * NWB + wave;
     if (unit >= a.units) return;  // whole wavefront
-    stream_unit<St, O32, NS, D, false>(a, unit, a.t_parity);
+    stream_unit<St, O32, NS, D, false, stream_in_step<St, NS>()>(a, unit, a.t_parity);
 }
 
 // Many 2D cavities, several steps per launch: wavefront w takes work unit w
@@ -1148,7 +1180,7 @@ void batch_stream_kernel(BatchStreamArgs<St> b) {
     // do not change during a launch)
     using CArgs = const __attribute__((address_space(4))) StreamArgs<St>;
     const StreamArgs<St>& a = *(const StreamArgs<St>*)((CArgs*)b.desc + ((uint32_t)b.src * b.count + k));
-    if (!stream_unit<St, O32, NS, D, true>(a, unit - b.unit0[k], b.t_parity)) b.unstable[k] = 1;
+    if (!stream_unit<St, O32, NS, D, true, false>(a, unit - b.unit0[k], b.t_parity)) b.unstable[k] = 1;
 }
 
 // --------------------------------------------------------- batched cavities
@@ -1388,7 +1420,8 @@ __global__ __launch_bounds__(kBlock) void diag_kernel(DiagArgs<St> a) {
     }
 }
 
-// one block: reduce nblk partial rows in block order
+// One block: reduce nblk partial rows in block order.  A chain of latencies;
+// with the six values one after the other it took 6.7 us.
 __global__ __launch_bounds__(1024) void diag_final_kernel(const double* partial, int nblk, double* out) {
     __shared__ double lds[1024 / 64];
     for (int v = 0; v < kDiagVals; ++v) {

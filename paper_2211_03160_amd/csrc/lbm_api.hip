@@ -570,30 +570,35 @@ bool streamable3(const lbm_ctx* c) {
 #define LBM_STREAM_AHEAD 1  // rows between a row's loads and their first use (two-step kernel)
 #endif
 
-// k launches of the register-row kernel of NS steps each (prefetch distance
-// D rows), A -> B, advancing t by NS k
 // Rows per strip segment (one wavefront each), by storage and steps per
-// launch, measured on the 8193^2 cell.  Every segment repeats the rows of
-// its dependency cone outside it and runs its last step over the pipeline
-// fill, so longer segments waste less arithmetic; launches that move many
-// bytes per update still run fastest with short ones (FP32 at three steps:
-// 117 / 111 / 107 / 97 GLUPS at 16 / 24 / 32 / 64 rows; FP64 at two: 39 /
-// 37 / 36 / 36).  FP32 at four steps: 147 / 147 / 143 / 128 at 16 / 24 /
-// 32 / 64; FP16-f+FP32-g at four: 150 / 165 / 171 / 171 at 16 / 32 / 48 /
-// 64; FP16 at three: 162 / 168 / 164 / 161 at 16 / 32 / 48 / 64, BF16 at
-// three 139 / 147 / 149 / 148.
-// With the written-out 2D collision: FP32 at four steps 149 / 145 / 138 /
-// 130 at 16 / 24 / 32 / 48 rows, at five 162 / 171 / 166 / 158; FP16 at
-// three 169 / 168 at 32 / 48; BF16 at four 185 at 48; FP16-f+FP32-g at
-// four 172 / 170 at 48 / 64.
-template <class St, int NS> constexpr uint32_t stream_seg_rows() {
+// launch, for a launch of strip_rows rows over all its strips.  Every segment
+// repeats the rows of its dependency cone outside it (NS - 1 on average) and
+// runs its last step over the pipeline fill, so longer segments waste less
+// arithmetic; but a launch ends with the last segments running on a part of
+// the wavefronts, half a segment's time on average.  With A rows per
+// resident wavefront the time goes as (A / r + 1/2) (r + NS - 1), least at
+// r = sqrt(2 (NS - 1) A).  FP32 at five steps (kept in step, so that long
+// segments do not cost memory traffic) follows that; GLUPS at 24 / 32 / 40 /
+// 56 / 72 rows: 4097^2 (rule 35) 150 / 149 / 152 / 145 / 158, 6145x5000 (47)
+// 164 / 168 / 172 / 170 / 168, 12000x6000 (72) 168 / 174 / 180 / 182 / 182,
+// 8193^2 (70) 168 / 172 / 179 / 178 / 180.
+// The other modes take one length, measured on 4097^2 and 8193^2: FP16 at
+// three 133 / 150 / 147 and 173 / 178 / 179 at 32 / 48 / 56 rows; BF16 at four
+// 155 / 150 / 163 and 182 / 193 / 195, FP16-f+FP32-g at four 144 / 139 / 152
+// and 167 / 177 / 178.  FP32 at three 117 / 111 / 107 / 97 at 16 / 24 / 32 / 64
+// on 8193^2, at four 149 / 145 / 138 at 16 / 24 / 32; FP64 at two 39 / 37 / 36 /
+// 36 at 16 / 24 / 32 / 64.
+template <class St, int NS> uint32_t stream_seg_rows(uint64_t strip_rows, int cus) {
     constexpr bool f32 = sizeof(typename St::TF) == 4 && sizeof(typename St::TG) == 4;
     constexpr bool f64 = sizeof(typename St::TF) == 8;
     constexpr bool half = sizeof(typename St::TF) == 2 && sizeof(typename St::TG) == 2;
     if constexpr (f64) return NS == 2 ? 16 : 64;
-    else if constexpr (f32) return NS == 5 ? 24 : 16;
-    else if constexpr (half) return NS == 2 ? 40 : NS == 3 ? 32 : 48;
-    else return NS == 2 ? 16 : NS == 3 ? 40 : 48;  // FP16 f, FP32 g
+    else if constexpr (f32 && NS == 5) {
+        const double A = (double)strip_rows / (4.0 * stream_waves_per_simd<St, NS>() * std::max(cus, 1));
+        return (uint32_t)std::min(72.0, std::max(24.0, std::sqrt(2.0 * (NS - 1) * A)));
+    } else if constexpr (f32) return 16;
+    else if constexpr (half) return NS == 2 ? 40 : NS == 3 ? 48 : 56;
+    else return NS == 2 ? 16 : NS == 3 ? 40 : 56;  // FP16 f, FP32 g
 }
 
 template <class St, int NS, int D> void stream_launches(lbm_ctx* c, int64_t k) {
@@ -603,8 +608,17 @@ template <class St, int NS, int D> void stream_launches(lbm_ctx* c, int64_t k) {
     a.geo = c->geo;
     a.c = make_coef<typename St::R>(c);
     a.strips = (c->geo.nx + W - 1) / W;
-    a.seg_rows = stream_seg_rows<St, NS>();
-    a.units = a.strips * ((c->geo.ny + a.seg_rows - 1) / a.seg_rows);
+    a.seg_rows = stream_seg_rows<St, NS>((uint64_t)a.strips * c->geo.ny, c->cus);
+    // The segments at walls in y get what is left over, in two halves: with
+    // wall rules a row takes 1.6 times as long, and the last segment's units
+    // are what the launch ends on.
+    a.first_rows = a.seg_rows;
+    if (!c->geo.periodic[1] && c->geo.ny >= 2 * a.seg_rows) {
+        const uint32_t over = c->geo.ny % a.seg_rows;
+        a.first_rows = (over < a.seg_rows / 2 ? over + a.seg_rows : over) / 2;
+    }
+    a.segs = 1 + (c->geo.ny > a.first_rows ? (c->geo.ny - a.first_rows + a.seg_rows - 1) / a.seg_rows : 0);
+    a.units = a.strips * a.segs;
     const uint32_t blocks = (a.units + NWB - 1) / NWB;
     a.blocks_per_xcd = (blocks + kXcd - 1) / kXcd;
     const dim3 grid(a.blocks_per_xcd * kXcd), block(64 * NWB);
@@ -642,6 +656,8 @@ template <class St, int RX, int RY, int KT> void tile2_launches(lbm_ctx* c, int6
     a.tiles = a.tiles_x * ((c->geo.ny + oy - 1) / oy);
     a.blocks_per_xcd = (a.tiles + kXcd - 1) / kXcd;
     a.flux = c->flux(0, 0);
+// k launches of the register-row kernel of NS steps each (prefetch distance
+// D rows), A -> B, advancing t by NS k
     a.slot[0] = 0;
     a.slot[1] = (uint32_t)c->lay.flux_doubles;
     const dim3 grid(a.blocks_per_xcd * kXcd), block(RX * RY);
