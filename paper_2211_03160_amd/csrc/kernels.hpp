@@ -1386,7 +1386,6 @@ __device__ __forceinline__ double block_reduce(double v, Op op, double* lds) {
 }
 
 struct AddOp { __device__ double operator()(double a, double b) const { return a + b; } };
-struct MaxOp { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
 
 constexpr int kDiagVals = 6;  // mass, energy, sum |u|^2, sum u_g (T - T0), max |u|, nonfinite
 
@@ -1399,9 +1398,28 @@ template <class St> struct DiagArgs {
     double* partial;  // [gridDim.x][kDiagVals]
 };
 
+// block_reduce of the six values together: their shuffles and LDS reads
+// overlap, and there is one pair of barriers in place of six.  The order of
+// each value's operations is block_reduce's.  Thread 0 holds the results.
+template <int NT> __device__ __forceinline__ void diag_reduce(double (&v)[kDiagVals], double* lds) {
+    constexpr int W = NT / 64;
+    auto op = [](int k, double a, double b) { return k == 4 ? fmax(a, b) : a + b; };
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int k = 0; k < kDiagVals; ++k) v[k] = op(k, v[k], __shfl_down(v[k], o, 64));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0)
+        for (int k = 0; k < kDiagVals; ++k) lds[wave * kDiagVals + k] = v[k];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < W; ++w)
+        for (int k = 0; k < kDiagVals; ++k) v[k] = op(k, v[k], lds[w * kDiagVals + k]);
+}
+
 template <int DIM, class St>
 __global__ __launch_bounds__(kBlock) void diag_kernel(DiagArgs<St> a) {
-    __shared__ double lds[kBlock / 64];
+    __shared__ double lds[kBlock / 64 * kDiagVals];
     double acc[kDiagVals] = {0, 0, 0, 0, 0, 0};
     for (uint32_t idx = blockIdx.x * kBlock + threadIdx.x; idx < a.geo.N; idx += gridDim.x * kBlock) {
         const auto m = node_moments<DIM, St>(a.fsrc, a.gsrc, a.geo, idx, a.gbeta, a.bt, a.t0);
@@ -1413,26 +1431,24 @@ __global__ __launch_bounds__(kBlock) void diag_kernel(DiagArgs<St> a) {
         acc[4] = fmax(acc[4], sqrt(uu));
         acc[5] += m.nonfinite;
     }
-    for (int v = 0; v < kDiagVals; ++v) {
-        const double r = v == 4 ? block_reduce<kBlock>(acc[v], MaxOp{}, lds)
-                                : block_reduce<kBlock>(acc[v], AddOp{}, lds);
-        if (threadIdx.x == 0) a.partial[(size_t)blockIdx.x * kDiagVals + v] = r;
-    }
+    diag_reduce<kBlock>(acc, lds);
+    if (threadIdx.x == 0)
+        for (int v = 0; v < kDiagVals; ++v) a.partial[(size_t)blockIdx.x * kDiagVals + v] = acc[v];
 }
 
 // One block: reduce nblk partial rows in block order.  A chain of latencies;
 // with the six values one after the other it took 6.7 us.
 __global__ __launch_bounds__(1024) void diag_final_kernel(const double* partial, int nblk, double* out) {
-    __shared__ double lds[1024 / 64];
-    for (int v = 0; v < kDiagVals; ++v) {
-        double acc = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += 1024) {
+    __shared__ double lds[1024 / 64 * kDiagVals];
+    double acc[kDiagVals] = {0, 0, 0, 0, 0, 0};
+    for (int b = threadIdx.x; b < nblk; b += 1024)
+        for (int v = 0; v < kDiagVals; ++v) {
             const double x = partial[(size_t)b * kDiagVals + v];
-            acc = v == 4 ? fmax(acc, x) : acc + x;
+            acc[v] = v == 4 ? fmax(acc[v], x) : acc[v] + x;
         }
-        const double r = v == 4 ? block_reduce<1024>(acc, MaxOp{}, lds) : block_reduce<1024>(acc, AddOp{}, lds);
-        if (threadIdx.x == 0) out[v] = r;
-    }
+    diag_reduce<1024>(acc, lds);
+    if (threadIdx.x == 0)
+        for (int v = 0; v < kDiagVals; ++v) out[v] = acc[v];
 }
 
 // The values of lbm_diag from the reduced sums (mass, energy, sum |u|^2,

@@ -7,6 +7,7 @@
 // The library never allocates device memory.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -184,6 +185,44 @@ Layout layout(const lbm_params* p, size_t staging_cap = kStagingNodes) {
     return L;
 }
 
+// Pinned host memory for the last kernel of a reduction to write its sums to,
+// so that the host needs no copy, only the wait for the stream (50 steps of
+// 65^2, Nusselt numbers, diagnostics and fields: 141 us; 163 with copies, and
+// the diagnostics' six sums reduced one after the other).
+// kSumsSlots contexts of a process have a slot each, taken when a context is
+// created and given back when it is destroyed (every call that uses it waits
+// for its kernel); the others (null) copy from the workspace.  The memory is
+// allocated with the first context and kept: freeing it would wait for the
+// device, and disturb a capture.
+constexpr int kSums = 16, kSumsSlots = 64;  // doubles per slot (two flux slots' 6 faces need 12); slots
+std::mutex g_sums_mu;
+double* g_sums = nullptr;
+bool g_sums_failed = false;
+uint64_t g_sums_taken = 0;  // a bit per slot
+
+double* take_sums() {
+    std::lock_guard<std::mutex> lock(g_sums_mu);
+    if (!g_sums && !g_sums_failed) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // an allocation is no part of a capture
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void* p = nullptr;
+        g_sums_failed = hipHostMalloc(&p, kSumsSlots * kSums * sizeof(double),
+                                      hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess;
+        if (g_sums_failed) (void)hipGetLastError();
+        else g_sums = (double*)p;
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (!g_sums || !~g_sums_taken) return nullptr;
+    const int k = __builtin_ctzll(~g_sums_taken);
+    g_sums_taken |= 1ull << k;
+    return g_sums + k * kSums;
+}
+
+void give_back_sums(const double* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(g_sums_mu);
+    g_sums_taken &= ~(1ull << ((p - g_sums) / kSums));
+}
 }  // namespace
 
 struct lbm_ctx {
@@ -202,8 +241,10 @@ struct lbm_ctx {
     bool steps_set;            // the count was set by the caller: launches take exactly it
     int cus;                   // compute units of the device
     bool poison;               // debug: fill the destination state with NaN before every launch
+    double* sums = nullptr;    // see take_sums
     char err[512];
 
+    ~lbm_ctx() { give_back_sums(sums); }
     void* pop(int k) const { return ws + lay.off_pop[k]; }
     double* flux(int slot, int face) const {
         double* base = (double*)(ws + lay.off_flux) + (size_t)slot * lay.flux_doubles;
@@ -476,6 +517,14 @@ lbm_status zero_flux(lbm_ctx* c) {
     return LBM_OK;
 }
 
+// n sums that a kernel writes to out (c->sums or device memory), on the host
+lbm_status wait_sums(lbm_ctx* c, const double* out, int n, double* host) {
+    if (out != c->sums) HIP_TRY(c->err, hipMemcpyAsync(host, out, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c->err, hipStreamSynchronize(c->stream));
+    if (out == c->sums) std::copy(out, out + n, host);
+    return LBM_OK;
+}
+
 // sums of the two flux slots of every face: out[slot * 6 + face]
 lbm_status face_sums(lbm_ctx* c, double* host12) {
     FaceSumArgs a{};
@@ -485,12 +534,10 @@ lbm_status face_sums(lbm_ctx* c, double* host12) {
             a.buf[b] = c->geo.dirichlet[f] ? c->flux(slot, f) : nullptr;
             a.count[b] = (uint32_t)c->lay.area[f];
         }
-    a.out = c->red();
+    a.out = c->sums ? c->sums : c->red();
     hipLaunchKernelGGL(face_sum_kernel, dim3(12), dim3(1024), 0, c->stream, a);
     HIP_TRY(c->err, hipGetLastError());
-    HIP_TRY(c->err, hipMemcpyAsync(host12, c->red(), 12 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c->err, hipStreamSynchronize(c->stream));
-    return LBM_OK;
+    return wait_sums(c, a.out, 12, host12);
 }
 
 }  // namespace
@@ -601,6 +648,8 @@ template <class St, int NS> uint32_t stream_seg_rows(uint64_t strip_rows, int cu
     else return NS == 2 ? 16 : NS == 3 ? 40 : 56;  // FP16 f, FP32 g
 }
 
+// k launches of the register-row kernel of NS steps each (prefetch distance
+// D rows), A -> B, advancing t by NS k
 template <class St, int NS, int D> void stream_launches(lbm_ctx* c, int64_t k) {
     constexpr int NWB = LBM_STREAM_WAVES;
     constexpr uint32_t W = strip_cols<NS>();
@@ -656,8 +705,6 @@ template <class St, int RX, int RY, int KT> void tile2_launches(lbm_ctx* c, int6
     a.tiles = a.tiles_x * ((c->geo.ny + oy - 1) / oy);
     a.blocks_per_xcd = (a.tiles + kXcd - 1) / kXcd;
     a.flux = c->flux(0, 0);
-// k launches of the register-row kernel of NS steps each (prefetch distance
-// D rows), A -> B, advancing t by NS k
     a.slot[0] = 0;
     a.slot[1] = (uint32_t)c->lay.flux_doubles;
     const dim3 grid(a.blocks_per_xcd * kXcd), block(RX * RY);
@@ -900,7 +947,9 @@ lbm_status reject_view(lbm_ctx* c, const char* what) {
 extern "C" {
 
 lbm_status lbm_create(const lbm_params* p, void* d_workspace, size_t bytes, void* hip_stream, lbm_ctx** out) {
-    return create_ctx(p, d_workspace, bytes, hip_stream, kStagingNodes, false, out);
+    const lbm_status st = create_ctx(p, d_workspace, bytes, hip_stream, kStagingNodes, false, out);
+    if (!st) (*out)->sums = take_sums();
+    return st;
 }
 
 void lbm_destroy(lbm_ctx* c) {
@@ -1190,14 +1239,12 @@ static lbm_status run_diag(lbm_ctx* c, double* host6) {
         a.t0 = c->d.v[LBM_D_T0];
         a.partial = c->red();
         const int nblk = (int)std::min<size_t>(kDiagBlocks, grid_for(c->geo.N));
-        double* out = c->red() + (size_t)kDiagBlocks * kDiagVals;
+        double* out = c->sums ? c->sums : c->red() + (size_t)kDiagBlocks * kDiagVals;
         hipLaunchKernelGGL((diag_kernel<DIM, St>), dim3(nblk), dim3(kBlock), 0, c->stream, a);
         HIP_TRY(c->err, hipGetLastError());
         hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(1024), 0, c->stream, (const double*)c->red(), nblk, out);
         HIP_TRY(c->err, hipGetLastError());
-        HIP_TRY(c->err, hipMemcpyAsync(host6, out, kDiagVals * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c->err, hipStreamSynchronize(c->stream));
-        return LBM_OK;
+        return wait_sums(c, out, kDiagVals, host6);
     });
 }
 
