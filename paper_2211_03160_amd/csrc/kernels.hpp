@@ -692,16 +692,16 @@ __device__ __forceinline__ GlobalSrc<St, QF, QG, O32, U24> global_src(const Geom
 // the node's Dirichlet links goes to the flux sink `fx`.  Walls = false is
 // for nodes known to have every link inside the domain (or across a
 // periodic face): it drops the wall rules and the flux at compile time.
-// Returns false if the new rho or T is not finite.
+// Returns false if the new rho or T is not finite.  step_node_at takes the
+// reference temperature at the node from the caller.
 template <int DIM, class St, bool Walls = true, class Src, class Dst, class Flux>
-__device__ __forceinline__ bool step_node(const Geometry& g, const Coef<typename St::R>& c, const Neighbours& nb,
-                                          uint32_t x, uint32_t y, uint32_t z, const Src& src, const Dst& dst,
-                                          const Flux& fx) {
+__device__ __forceinline__ bool step_node_at(const Geometry& g, const Coef<typename St::R>& c, const Neighbours& nb,
+                                             typename St::R tb, uint32_t x, uint32_t y, uint32_t z, const Src& src,
+                                             const Dst& dst, const Flux& fx) {
     using R = typename St::R;
     using L = Flow<DIM>;
     using H = Heat<DIM>;
     R hf[L::Q], hg[H::Q];
-    const R tb = base_temp(c.bt, x, y, z);
     // The gather is free of branches: a link that crosses a wall reads the
     // opposite plane at the node itself (bounce-back) through the same
     // single load, so every load is issued before any result is waited
@@ -743,6 +743,13 @@ __device__ __forceinline__ bool step_node(const Geometry& g, const Coef<typename
             fx.template put<face>(g, local, abb + c.flux_c[face] - 2.0 * (double)wall_v[i], wall_abb[i]);
         });
     return collide_store<DIM, St>(hf, hg, c, tb, dst);
+}
+
+template <int DIM, class St, bool Walls = true, class Src, class Dst, class Flux>
+__device__ __forceinline__ bool step_node(const Geometry& g, const Coef<typename St::R>& c, const Neighbours& nb,
+                                          uint32_t x, uint32_t y, uint32_t z, const Src& src, const Dst& dst,
+                                          const Flux& fx) {
+    return step_node_at<DIM, St, Walls>(g, c, nb, base_temp(c.bt, x, y, z), x, y, z, src, dst, fx);
 }
 
 // the update of node idx of the arrays fsrc/gsrc into fdst/gdst
@@ -977,6 +984,11 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
     const int32_t col = region_coord(cx, g.nx, g.periodic[0]);  // -1 beyond a wall
     const uint32_t ucol = col < 0 ? 0u : (uint32_t)col;         // any in-domain column for dead lanes
     const bool own_col = lane >= NS && lane < NS + W && cx < (int32_t)g.nx;
+    // The reference temperature in row y, tb_x + tb_y y: its x part (all of
+    // it where it varies along x) once per strip, so a row costs a conversion
+    // and a multiply-add.
+    const R tb_x = a.c.bt.axis == 0 ? base_temp(a.c.bt, ucol, 0u, 0u) : a.c.bt.tb0;
+    const R tb_y = a.c.bt.axis == 1 ? a.c.bt.tbg : (R)0;
 
     // Rings: NI input rows, R rows of each intermediate step; the loop is
     // unrolled over U = NI iterations so that every ring index is a
@@ -1070,7 +1082,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
             const int32_t yj = y1 - 2 * (j - 1);
             const bool own = own_col && yj >= y0 && yj < y0 + rows;
             const uint32_t yy = (uint32_t)min(max(yj, 0), last);
-            const uint32_t x = own_col ? (uint32_t)cx : ucol;
+            const uint32_t x = ucol;  // own columns lie in the domain
             const Neighbours nb = neighbours(g, x, yy, 0);
             const RegSrc<St, QF, QG> src{fs[j - 2][st(3)], fs[j - 2][st(2)], fs[j - 2][st(1)],
                                          gs[j - 2][st(3)], gs[j - 2][st(2)], gs[j - 2][st(1)]};
@@ -1082,7 +1094,8 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
                 typename St::TF ef[QF];
                 typename St::TG eg[QG];
                 if (needed(NS, yj)) {
-                    const bool ok = step_node<2, St, Wl>(g, a.c, nb, x, yy, 0u, src, EncDst<St, QF, QG>{ef, eg}, fx);
+                    const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb_x + tb_y * (R)yy, x, yy, 0u, src,
+                                                            EncDst<St, QF, QG>{ef, eg}, fx);
                     if constexpr (Report) bad = bad || (own && !ok);
                 } else {
                     // stored to the dropped offset: any value will do, so
@@ -1098,7 +1111,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
                 static_for<0, QG>([&](auto ic) { dst.sg(decltype(ic)::value, eg[decltype(ic)::value]); });
             } else if (needed(j, yj)) {
                 const RegDst<St, QF, QG> dst{fs[j - 1][st(0)], gs[j - 1][st(0)]};
-                const bool ok = step_node<2, St, Wl>(g, a.c, nb, x, yy, 0u, src, dst, fx);
+                const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb_x + tb_y * (R)yy, x, yy, 0u, src, dst, fx);
                 // an intermediate state is checked too where it is a real
                 // node's: a valid lane of step j inside the domain
                 if constexpr (Report)
@@ -1116,7 +1129,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
                                          gin[in(2 + D)], gin[in(1 + D)], gin[in(D)]};
             const RegDst<St, QF, QG> dst{fs[0][st(0)], gs[0][st(0)]};
             const bool own = own_col && y1 >= y0 && y1 < y0 + rows;
-            const bool ok = step_node<2, St, Wl>(g, a.c, nb, ucol, yy, 0u, src, dst,
+            const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb_x + tb_y * (R)yy, ucol, yy, 0u, src, dst,
                                                  BufFlux2{rflux, a.slot[(tp + 1) & 1], a.flux_bytes, own});
             if constexpr (Report) bad = bad || (!ok && lane >= 1 && lane <= 62 && col >= 0 && r1 >= 0);
         }
