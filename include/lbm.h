@@ -16,9 +16,9 @@
  * Every time step is one fused pass: pull-streaming (Eqs. 8b, 9b) with the
  * wall rules, the moments, both collisions and the store of the
  * post-collision populations.  In 2D one kernel launch runs two to five
- * such steps (lbm_set_steps_per_launch), keeping the intermediate rows in
- * registers; in 3D one launch runs two (FP32 storage, the first step's
- * planes in LDS and registers) or one.
+ * such steps (lbm_set_steps_per_launch), keeping the intermediate steps in
+ * LDS (small and mid-size grids) or registers; in 3D one launch runs two
+ * (FP32 storage, the first step's planes in LDS and registers) or one.
  *
  * Conventions
  *   - Every function returns an lbm_status (or a documented value); none
@@ -26,7 +26,10 @@
  *   - The library NEVER allocates device memory.  The caller provides one
  *     device workspace of lbm_workspace_bytes() bytes (e.g. a uint8 tensor)
  *     and a HIP stream; both must outlive the context.  Host memory of the
- *     context itself is owned by the library and freed by lbm_destroy().
+ *     context itself is owned by the library and freed by lbm_destroy();
+ *     8 KiB of pinned host memory per process, for the sums that
+ *     lbm_nusselt, lbm_wall_flux and lbm_diagnostics wait for, are
+ *     allocated with the first context and kept.
  *   - All kernels run on the caller's stream, in stream order.  lbm_step()
  *     only enqueues; lbm_fields/lbm_nusselt/lbm_diagnostics/lbm_wall_flux/
  *     lbm_export_state synchronise the stream before returning.
