@@ -1,0 +1,55 @@
+"""Batches whose configuration changes between steps: captured graphs, the
+autotuner's choice and explicit counts must leave the state where single steps
+put it, bit for bit."""
+import pytest
+
+from paper_2211_03160_amd import lbm, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(33, 17), (66, 33), (41, 41), (130, 57)]
+LARGE = [(513, 513)] * 16  # streaming beats one step per launch, tiles beat streaming
+
+
+def _batch(storage, shapes=SHAPES):
+    b = lbm.Batch([W.rayleigh_benard(2, s, ra=5e4, pr=0.71, storage=storage) for s in shapes])
+    return b
+
+
+def _init(b):
+    b.init([3 + k for k in range(b.count)], [2e-2] * b.count)
+
+
+def _same_as_single_steps(b, storage, shapes=SHAPES):
+    one = _batch(storage, shapes)
+    one.steps_per_launch = 1
+    _init(one)
+    one.step(b.t)
+    for k in range(b.count):
+        same = b.cavity(k).export_state() == one.cavity(k).export_state()
+        assert same, f"cavity {k} at t = {b.t}"
+
+
+@pytest.mark.parametrize("storage,shapes,graph_steps", [
+    ("fp32", SHAPES, 10), ("fp64", SHAPES, 10), ("fp16", LARGE, 4), ("bf16", LARGE, 12), ("fp32", LARGE, 20)])
+def test_reapplied_configuration_after_tuning(storage, shapes, graph_steps):
+    """Graphs captured after tuning, then the batch's own configuration set
+    again, whole and with the streaming shape only: a graph of launches of
+    another kind must not be replayed, whatever the parity of its launches."""
+    b = _batch(storage, shapes)
+    _init(b)
+    b.set_config(graph_steps=graph_steps)
+    b.tune(steps=3)
+    b.step(2 * graph_steps)
+    cfg = b.config()
+    b.set_config(**cfg)
+    b.step(graph_steps)
+    _same_as_single_steps(b, storage, shapes)
+    keys = ("block", "grid_per_cu", "graph_steps", "stream_rows", "stream_waves")
+    b.set_config(**{k: cfg[k] for k in keys})
+    b.step(2 * graph_steps)
+    _same_as_single_steps(b, storage, shapes)
+    # a count that is set, with graphs of the former launches at hand
+    b.steps_per_launch = 2
+    b.step(2 * graph_steps + 3)
+    _same_as_single_steps(b, storage, shapes)
