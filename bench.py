@@ -174,7 +174,7 @@ def batched_sweep(K, warmup, noise):
     b = lbm.Batch(cfgs)
     b.init(seeds, [noise] * len(cfgs))
     best, cand_ms = b.tune(steps=3)
-    spl_tuned = b.steps_per_launch
+    spl_tuned = b.launch_steps
     b.set_config(**{**best, "graph_steps": graph_steps})
     ms_tuned = timed(b)
     flagged = int(b.unstable().sum())

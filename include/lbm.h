@@ -327,7 +327,10 @@ typedef struct lbm_batch_config {
                             launches of G steps once into a hipGraph and
                             replay it (needs a non-default stream; ignored on
                             the NULL stream)                                  */
-    int32_t reserved;    /* 0                                                 */
+    int32_t tiles;       /* 0: LDS tile launches where the batch has them, no
+                            count was set and stream_rows and stream_waves
+                            are 0; 1: the same whatever these two are (what
+                            lbm_batch_tune writes when tiles win)             */
     int32_t stream_rows;  /* rows per strip segment of the streaming kernel
                              (several steps per launch), 8 .. 256; 0: the
                              default of the storage mode                      */
@@ -358,9 +361,13 @@ lbm_status lbm_batch_init_fields(lbm_batch* b, int32_t k, const double* rho, con
  * launches of several steps, then one-step launches for the remainder).  A
  * 2D batch of at most 9 to 15 million nodes (any number with FP64 storage)
  * takes 4 or 5 steps per launch through LDS tiles until a count or a
- * streaming shape is set; else launches take
+ * streaming shape is set (lbm_batch_config); else launches take
  * lbm_batch_get_steps_per_launch steps.  Asynchronous.                  */
 lbm_status lbm_batch_step(lbm_batch* b, int64_t n);
+
+/* Steps that a launch of lbm_batch_step advances now: the tiles' 4 or 5, or
+ * lbm_batch_get_steps_per_launch.  0 for NULL.                          */
+int32_t lbm_batch_launch_steps(const lbm_batch* b);
 
 /* Steps per launch of lbm_batch_step: 1 (batch_step_kernel, the shape of
  * lbm_batch_config) or 2..5 (the streaming kernel; 2D batches whose
@@ -370,7 +377,9 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t n);
  * depend on it (bitwise).  LBM_E_INVALID outside 1..5, LBM_E_UNSUPPORTED
  * for k > 1 where streaming is not available, for k > 2 with FP64 storage
  * and for k = 5 with 16-bit storage.  Synchronises the batch stream when
- * the count changes (the work tables are rewritten).                    */
+ * the count changes (the work tables are rewritten).  A count that was set
+ * is taken exactly, whatever the configuration says of tiles, until
+ * lbm_batch_tune chooses anew.                                          */
 lbm_status lbm_batch_set_steps_per_launch(lbm_batch* b, int32_t steps);
 int32_t lbm_batch_get_steps_per_launch(const lbm_batch* b); /* 0 for NULL */
 
@@ -399,8 +408,10 @@ lbm_status lbm_batch_unstable(lbm_batch* b, int32_t* flags);
  * per launch (graph_steps is left as configured); results do not depend on
  * any of them (bitwise).  Where the batch can run through LDS tiles
  * (lbm_batch_step), those launches are timed too, without advancing t and
- * without an entry in ms_per_step, and stay in use if they are faster than
- * every candidate.  The timing steps are real steps: t advances by
+ * without an entry in ms_per_step, and are used from then on if they are
+ * faster than every candidate: `best` then has tiles = 1 beside the fastest
+ * candidate's shape, and a configuration that is given back with
+ * lbm_batch_set_config keeps the launches it stands for.  The timing steps are real steps: t advances by
  * (steps + 1) x the steps per launch of every candidate.  ms_per_step
  * (nullable) receives up to LBM_BATCH_TUNE_MAX timings in candidate order,
  * ncand their number.                                                   */

@@ -36,6 +36,7 @@ EXPORTS = ["lbm_derive", "lbm_workspace_bytes", "lbm_bytes_per_update",
            "lbm_batch_cavity", "lbm_batch_nusselt", "lbm_batch_unstable",
            "lbm_batch_tune", "lbm_batch_set_config", "lbm_batch_get_config",
            "lbm_batch_set_steps_per_launch", "lbm_batch_get_steps_per_launch",
+           "lbm_batch_launch_steps",
            "lbm_batch_time", "lbm_batch_destroy", "lbm_batch_last_error",
            "lbm_probe_bandwidth", "lbm_diagnostics_async"]
 DIAG_VALUES = 7  # LBM_DIAG_VALUES: t, mass, energy, umax, nu_vol, re, nonfinite
@@ -64,13 +65,16 @@ class Diag(C.Structure):
 
 class BatchConfig(C.Structure):
     _fields_ = [("block", C.c_int32), ("grid_per_cu", C.c_int32),
-                ("graph_steps", C.c_int32), ("reserved", C.c_int32),
+                ("graph_steps", C.c_int32), ("tiles", C.c_int32),
                 ("stream_rows", C.c_int32), ("stream_waves", C.c_int32)]
 
     def as_dict(self):
-        return {"block": self.block, "grid_per_cu": self.grid_per_cu,
-                "graph_steps": self.graph_steps, "stream_rows": self.stream_rows,
-                "stream_waves": self.stream_waves}
+        d = {"block": self.block, "grid_per_cu": self.grid_per_cu,
+             "graph_steps": self.graph_steps, "stream_rows": self.stream_rows,
+             "stream_waves": self.stream_waves}
+        if self.tiles:  # only where the autotuner chose them beside a streaming shape
+            d["tiles"] = self.tiles
+        return d
 
 
 BATCH_TUNE_MAX = 80  # LBM_BATCH_TUNE_MAX
@@ -144,6 +148,8 @@ def lib():
         L.lbm_batch_set_steps_per_launch.argtypes = [P, C.c_int32]
         L.lbm_batch_get_steps_per_launch.argtypes = [P]
         L.lbm_batch_get_steps_per_launch.restype = C.c_int32
+        L.lbm_batch_launch_steps.argtypes = [P]
+        L.lbm_batch_launch_steps.restype = C.c_int32
         L.lbm_batch_time.argtypes = [P]
         L.lbm_batch_time.restype = C.c_int64
         L.lbm_batch_destroy.argtypes = [P]
@@ -462,12 +468,18 @@ class Batch:
 
     @property
     def steps_per_launch(self) -> int:
-        """Steps per launch of step(): 1, or 2..5 (streaming, 2D)."""
+        """Steps per launch of step() unless it goes through LDS tiles
+        (launch_steps): 1, or 2..5 (streaming, 2D)."""
         return int(lib().lbm_batch_get_steps_per_launch(self._h))
 
     @steps_per_launch.setter
     def steps_per_launch(self, k: int):
         self._check(lib().lbm_batch_set_steps_per_launch(self._h, int(k)))
+
+    @property
+    def launch_steps(self) -> int:
+        """Steps that a launch of step() advances now."""
+        return int(lib().lbm_batch_launch_steps(self._h))
 
     def cavity(self, k: int) -> Cavity:
         h = C.c_void_p()
@@ -490,14 +502,16 @@ class Batch:
         self._check(lib().lbm_batch_get_config(self._h, C.byref(c)))
         return c.as_dict()
 
-    def set_config(self, block=256, grid_per_cu=0, graph_steps=0, stream_rows=0, stream_waves=0):
-        c = BatchConfig(int(block), int(grid_per_cu), int(graph_steps), 0, int(stream_rows), int(stream_waves))
+    def set_config(self, block=256, grid_per_cu=0, graph_steps=0, stream_rows=0, stream_waves=0, tiles=0):
+        c = BatchConfig(int(block), int(grid_per_cu), int(graph_steps), int(tiles), int(stream_rows),
+                        int(stream_waves))
         self._check(lib().lbm_batch_set_config(self._h, C.byref(c)))
 
     def tune(self, steps: int = 5):
         """Autotune (lbm_batch_tune): returns the chosen configuration (its
-        steps per launch is self.steps_per_launch afterwards) and the
-        per-step timings of every candidate, in ms."""
+        steps per launch is self.launch_steps afterwards; without "tiles"
+        in it, another batch needs that set besides) and the per-step timings of
+        every candidate, in ms."""
         best = BatchConfig()
         ms = np.zeros(BATCH_TUNE_MAX)
         n = C.c_int32()

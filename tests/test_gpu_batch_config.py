@@ -45,11 +45,54 @@ def test_reapplied_configuration_after_tuning(storage, shapes, graph_steps):
     b.set_config(**cfg)
     b.step(graph_steps)
     _same_as_single_steps(b, storage, shapes)
-    keys = ("block", "grid_per_cu", "graph_steps", "stream_rows", "stream_waves")
-    b.set_config(**{k: cfg[k] for k in keys})
+    cfg.pop("tiles", None)
+    b.set_config(**cfg)
     b.step(2 * graph_steps)
     _same_as_single_steps(b, storage, shapes)
     # a count that is set, with graphs of the former launches at hand
     b.steps_per_launch = 2
     b.step(2 * graph_steps + 3)
     _same_as_single_steps(b, storage, shapes)
+
+
+@pytest.mark.parametrize("storage,shapes", [("fp16", LARGE), ("fp64", SHAPES)])
+def test_tuned_choice_is_part_of_the_configuration(storage, shapes):
+    """Giving the tuner's configuration back, changed in its graphs only,
+    keeps the launches it chose, on this batch and on a new one."""
+    b = _batch(storage, shapes)
+    _init(b)
+    assert b.config() == dict(block=256, grid_per_cu=0, graph_steps=0, stream_rows=0, stream_waves=0)
+    tiles = b.launch_steps
+    assert tiles in (4, 5) and tiles != b.steps_per_launch
+    best, _ = b.tune(steps=3)
+    chosen = b.launch_steps
+    assert chosen == (tiles if "tiles" in best else b.steps_per_launch)
+    b.set_config(**{**best, "graph_steps": 8})
+    assert b.launch_steps == chosen
+    b.step(27)
+    _same_as_single_steps(b, storage, shapes)
+    c = _batch(storage, shapes)
+    if "tiles" not in best:
+        c.steps_per_launch = b.steps_per_launch
+    c.set_config(**best)
+    assert c.launch_steps == chosen
+
+
+def test_launch_kind_follows_the_configuration():
+    b = _batch("fp16")
+    tiles, count = b.launch_steps, b.steps_per_launch
+    b.set_config(graph_steps=4, block=128)
+    assert b.launch_steps == tiles
+    b.set_config(stream_rows=24)
+    assert b.launch_steps == count
+    b.set_config(**b.config())
+    assert b.launch_steps == count
+    b.set_config(stream_rows=24, tiles=1)
+    assert b.launch_steps == tiles
+    with pytest.raises(lbm.LBMError):
+        b.set_config(stream_rows=5, stream_waves=4)  # refused: nothing changes
+    assert b.launch_steps == tiles
+    b.steps_per_launch = count  # a count that is set is taken exactly
+    assert b.launch_steps == count
+    b.set_config(tiles=1)
+    assert b.launch_steps == count
