@@ -403,9 +403,9 @@ struct WGradArgs {
 // LDS pixels carry 32 bytes of padding, so four consecutive pixels of a
 // transposing read fall into different banks.
 using lds_v4s = __attribute__((address_space(3))) v4s;
-__device__ __forceinline__ v4u lds_transposed(const unsigned char* p, uint32_t next) {
+__device__ __forceinline__ v4u lds_transposed(const unsigned char* p, const unsigned char* p4) {
     const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
-    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + next));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p4);
     struct P { v4s lo, hi; } r{lo, hi};
     return __builtin_bit_cast(v4u, r);
 }
@@ -419,7 +419,9 @@ void wgrad_kernel(WGradArgs a) {
     constexpr uint32_t SD = COB * 2 + 32, SX = CIB * 2 + 32;  // bytes per LDS pixel
     constexpr int ND = TW * TH * (COB / 8), NX = (TW + 2) * (TH + 2) * (CIB / 8);  // 16-byte pieces
     constexpr int PD = (ND + 255) / 256, PX = (NX + 255) / 256;
-    constexpr uint32_t kXAt = TW * TH * SD, kTileBytes = kXAt + (TW + 2) * (TH + 2) * SX;
+    constexpr uint32_t kXAt = TW * TH * SD, kZeroAt = kXAt + (TW + 2) * (TH + 2) * SX;
+    constexpr uint32_t kZeroBytes = (2 * (TW + 2) + 2) * SX + 48;  // as far as a lane's reads of the nine taps go
+    constexpr uint32_t kTileBytes = kZeroAt + kZeroBytes;
     constexpr uint32_t kSumBytes = WCO * WCI * 64 * 48 * 4;  // three taps of one wavefront per channel tile
     __shared__ __align__(16) unsigned char lds[kTileBytes > kSumBytes || WK == 1 ? kTileBytes : kSumBytes];
     const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -445,6 +447,8 @@ void wgrad_kernel(WGradArgs a) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) ones[k] = 0x3f803f80u;
     const bool with_bias = a.bias && ib == 0 && wci == 0;
+
+    for (uint32_t k = threadIdx.x; k < kZeroBytes / 16; k += 256) *(v4u*)(lds + kZeroAt + k * 16) = v4u{0u, 0u, 0u, 0u};
 
     v4u dv[PD], xv[PX];
     uint32_t tx = 0, ty = 0;
@@ -491,10 +495,17 @@ void wgrad_kernel(WGradArgs a) {
             const uint32_t kx = ks % KX * 8, ky = ks / KX * 4;
             if (ty * TH + ky >= (uint32_t)a.h || tx * TW + kx >= (uint32_t)a.w) continue;  // all outside
             const unsigned char* pd = lds + ((ky + kg) * TW + kx + (i >> 2)) * SD + wco * 64 + (i & 3) * 8;
+            // this lane's pixels of the K step, four apart.  Outside the image
+            // dz is 0, but the x beside it may lie inside, and 0 times an
+            // infinity must not reach a tap that does not use it: there a
+            // lane points at zeros.
             const unsigned char* px = lds + kXAt + ((ky + kg) * (TW + 2) + kx + (i >> 2)) * SX + wci * 64 + (i & 3) * 8;
+            const uint32_t in = ty * TH + ky + kg < (uint32_t)a.h ? (uint32_t)a.w - tx * TW - kx : 0u;
+            const unsigned char* px4 = (i >> 2) + 4 < in ? px + 4 * SX : lds + kZeroAt;
+            px = (i >> 2) < in ? px : lds + kZeroAt;
             v4u av[2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) av[u] = lds_transposed(pd + u * 32, 4 * SD);
+            for (int u = 0; u < 2; ++u) av[u] = lds_transposed(pd + u * 32, pd + u * 32 + 4 * SD);
             if (with_bias) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u) accb[u] = mfma32(av[u], ones, accb[u]);
@@ -503,11 +514,22 @@ void wgrad_kernel(WGradArgs a) {
             for (int tap = 0; tap < 9; ++tap) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
-                    const v4u bv = lds_transposed(px + (tap / 3 * (TW + 2) + tap % 3) * SX + s * 32, 4 * SX);
+                    const uint32_t at = (tap / 3 * (TW + 2) + tap % 3) * SX + s * 32;
+                    const v4u bv = lds_transposed(px + at, px4 + at);
 #pragma unroll
                     for (int u = 0; u < 2; ++u) acc[tap][u][s] = mfma32(av[u], bv, acc[tap][u][s]);
                 }
             }
+            // x fragments are read three ahead of the MFMAs that use them; the
+            // compiler's own order has one, for want of registers (64 -> 64
+            // channels at 16 x 136 x 136: 46 us, 56 in that order)
+            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+            for (int k = 0; k < 15; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
         }
     }
     // the sums of the wavefronts that split the K steps, three taps at a time, in order

@@ -1,0 +1,44 @@
+"""Values, alignments and shapes at the edges of what the network kernels take:
+infinities beside padding, tensors off 16-byte addresses, images of a few
+pixels, and sizes beyond one launch's grid.  Tolerances are those of the
+kernels' FP32 sums of exact BF16 products: 1e-5 of the sum of |terms|, and one
+BF16 rounding (2^-8 relative) where the output is BF16."""
+import numpy as np
+import pytest
+
+from oracle import nn_ref as R
+from tests.test_gpu_nn import BF, _bf, _dev_bf16, _host, _w_gpu_to_ref
+
+pytestmark = pytest.mark.gpu
+
+
+def _wgrad(x, dz, co, chunks=3):
+    import torch
+    from paper_2211_03160_amd import nn
+    n, h, w, ci = x.shape
+    dw, db = torch.empty((9, co, ci), device="cuda"), torch.empty((co,), device="cuda")
+    partial = torch.full((chunks * 9 * co * ci,), float("nan"), device="cuda")
+    nn._check(nn.lib().lbm_nn_conv3x3_wgrad(nn._p(x), nn._p(dz), n, h, w, ci, co, nn._p(partial), chunks, nn._p(dw),
+                                            nn._p(db), nn._s()))
+    return dw.cpu().numpy().astype(np.float64).reshape(3, 3, co, ci).transpose(0, 1, 3, 2), db.cpu().numpy()
+
+
+# the last row and column of images off whole 8 x 16 (16 x 16) pixel tiles,
+# and of whole ones
+@pytest.mark.parametrize("n,h,w,ci,co", [(1, 5, 7, 16, 16), (2, 17, 9, 32, 64), (2, 16, 8, 64, 64), (3, 3, 10, 64, 16)])
+def test_wgrad_infinite_activation_reaches_only_its_taps(n, h, w, ci, co):
+    rng = np.random.default_rng(h * w)
+    x = _bf(rng.standard_normal((n, h, w, ci)))
+    dz = _bf(1.0 + rng.random((n, h, w, co)))  # positive: an infinity never meets its negative
+    zero = np.zeros((3, 3, ci, co))
+    for i, j in ((h - 1, w - 1), (0, w - 1), (h - 1, 0), (0, 0), (h - 1, w // 2), (h // 2, w - 1)):
+        for b in {0, n - 1}:
+            xi = x.copy()
+            xi[b, i, j, ci // 2] = np.inf
+            _, ref, _ = R.conv3x3_backward(xi, zero, dz)
+            _, scale, _ = R.conv3x3_backward(np.abs(x), zero, np.abs(dz))
+            got, _ = _wgrad(_dev_bf16(xi), _dev_bf16(dz), co)
+            far = np.isinf(ref)
+            assert far.any() and not far.all() and not np.isnan(ref).any()
+            assert np.array_equal(got[far], ref[far]), (b, i, j)
+            assert np.all(np.abs(got[~far] - ref[~far]) <= 1e-5 * scale[~far] + 1e-6), (b, i, j)
