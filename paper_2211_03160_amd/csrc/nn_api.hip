@@ -66,7 +66,9 @@ template <int WM, int WN, int MT, int NT> bool conv3x3_lds_go(ConvArgs a, uint32
 }
 
 // The LDS convolution where it applies: whole K steps inside a tap (cin a
-// multiple of 32) and operands that fit the LDS.  The block follows the
+// multiple of 32), operands that fit the LDS, and addresses that allow its
+// 16-byte loads and the 8-byte accesses to mask and output (conv3x3_kernel
+// goes through those one value at a time).  The block follows the
 // shape; us for pixels x channels (wavefronts, tiles per wavefront):
 //   32 input channels: the stages are short, so each takes 256 pixels: 32 ->
 //     96 at 16 x 136 x 136 41 with 256 x 32, 52 with 128 x 32;
@@ -80,6 +82,7 @@ template <int WM, int WN, int MT, int NT> bool conv3x3_lds_go(ConvArgs a, uint32
 //     23.0 with conv3x3_kernel).
 bool conv3x3_lds(const ConvArgs& a, hipStream_t s) {
     if (a.cin % 32 || 18.0 * a.cin * a.cout > 4.0e9) return false;
+    if (!aligned16(a.x) || !aligned16(a.wt) || (uintptr_t)a.mask % 8 || (uintptr_t)a.y % 8) return false;
     const uint32_t taps = a.cin <= 96 ? 3 : 1;
     if (a.cout % 32) return conv3x3_lds_go<4, 1, 4, 1>(a, taps, s) || conv3x3_lds_go<4, 1, 1, 1>(a, 1, s);
     const uint64_t few = 512, wide = ((uint64_t)a.P + 255) / 256 * ((uint32_t)a.cout / 32);

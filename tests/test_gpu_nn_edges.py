@@ -42,3 +42,36 @@ def test_wgrad_infinite_activation_reaches_only_its_taps(n, h, w, ci, co):
             assert far.any() and not far.all() and not np.isnan(ref).any()
             assert np.array_equal(got[far], ref[far]), (b, i, j)
             assert np.all(np.abs(got[~far] - ref[~far]) <= 1e-5 * scale[~far] + 1e-6), (b, i, j)
+
+
+@pytest.mark.parametrize("ci,co", [(32, 32), (64, 48), (16, 32)])
+@pytest.mark.parametrize("skew", [1, 2, 4])
+def test_convolution_output_and_mask_off_8_byte_addresses(ci, co, skew):
+    """An output and a mask that only a value's own size aligns: the bits of
+    the aligned call, and no value beside the output."""
+    import torch
+    from paper_2211_03160_amd import nn
+    rng = np.random.default_rng(ci + skew)
+    n, h, w = 2, 9, 11
+    x, wt = _dev_bf16(rng.standard_normal((n, h, w, ci))), _dev_bf16(rng.standard_normal((9, co, ci)) * 0.2)
+    b = torch.from_numpy(rng.standard_normal(co).astype(np.float32)).cuda()
+    mask = _dev_bf16(rng.standard_normal((n, h, w, co)))
+    size = mask.numel()
+
+    def off(t=None):
+        flat = torch.full((size + 8,), 0x7abc, dtype=torch.int16, device="cuda")
+        if t is not None:
+            flat[skew:skew + size] = t.flatten()
+        return flat, flat[skew:skew + size].view(n, h, w, co)
+
+    flat, y = off()
+    nn._check(nn.lib().lbm_nn_conv3x3(nn._p(x), n, h, w, ci, nn._p(wt), nn._p(b), co, 1, nn._p(y), nn._s()))
+    assert torch.equal(y, nn.conv3x3(x, wt, b, co, True))
+    assert (flat[:skew] == 0x7abc).all() and (flat[skew + size:] == 0x7abc).all()
+    _, m = off(mask)
+    want = nn.conv3x3_masked(x, wt, mask, co)
+    assert torch.equal(nn.conv3x3_masked(x, wt, m, co), want)
+    flat, y = off()
+    nn._check(nn.lib().lbm_nn_conv3x3_masked(nn._p(x), n, h, w, ci, nn._p(wt), nn._p(m), co, nn._p(y), nn._s()))
+    assert torch.equal(y, want)
+    assert (flat[:skew] == 0x7abc).all() and (flat[skew + size:] == 0x7abc).all()
