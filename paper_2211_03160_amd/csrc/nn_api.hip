@@ -41,14 +41,23 @@ bool pos(int32_t v) { return v > 0; }
 
 bool aligned16(const void* p) { return (uintptr_t)p % 16 == 0; }
 
-// the grid of the row kernels: a block row per image row of n x h, runs of
-// 256 channel groups of 8 along it.  false: channels not a multiple of 8, or
-// the grid is too large (the element kernels take those).
-bool row_grid(int64_t n, int64_t h, int64_t w, int64_t c, dim3* grid) {
-    if (c % 8 || h > 0x7fffffff / n) return false;
-    const int64_t runs = (w * (c / 8) + 255) / 256;
-    if (runs > 65535 || w * (c / 8) > 0x7fffff00) return false;
-    *grid = dim3((unsigned)(n * h), (unsigned)runs);
+Div31 div31(uint32_t d) {
+    uint32_t s = 0;
+    while (s < 31 && (1u << s) < d) ++s;
+    return {(uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), 31 + s};
+}
+
+// the passes over an output of n x h x w pixels and c channels, a thread per
+// eight channels.  false: channels not a multiple of 8, or 2^31 groups of them
+// and more (the element kernels take those).
+bool row_grid(int64_t n, int64_t h, int64_t w, int64_t c, RowShape* a, dim3* grid) {
+    if (c % 8 || (double)n * h * w * (c / 8) >= 2147483648.0) return false;
+    a->items = (uint32_t)(n * h * w * (c / 8));
+    a->c8 = (uint32_t)(c / 8);
+    a->w = (uint32_t)w;
+    a->by_c8 = div31(a->c8);
+    a->by_w = div31(a->w);
+    *grid = dim3((a->items + 255) / 256);
     return true;
 }
 
@@ -233,10 +242,10 @@ lbm_status lbm_nn_avgpool2(const uint16_t* x, int32_t n, int32_t h, int32_t w, i
                            void* stream) {
     if (!x || !y || !pos(n) || !pos(h) || !pos(w) || !pos(c) || h % 2 || w % 2)
         return nn_fail(LBM_E_INVALID, "avgpool2: bad arguments");
+    RowShape rows;
     dim3 grid;
-    if (aligned16(x) && aligned16(y) && row_grid(n, h / 2, w / 2, c, &grid))
-        hipLaunchKernelGGL(pool_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, y, (uint32_t)h / 2, (uint32_t)w / 2,
-                           (uint32_t)c);
+    if (aligned16(x) && aligned16(y) && row_grid(n, h / 2, w / 2, c, &rows, &grid))
+        hipLaunchKernelGGL(pool_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, y, rows);
     else
         hipLaunchKernelGGL(avgpool2_kernel, dim3(grid1((size_t)n * h * w * c / 4)), dim3(256), 0, (hipStream_t)stream,
                            x, y, n, h, w, c);
@@ -247,10 +256,11 @@ lbm_status lbm_nn_avgpool2_backward(const uint16_t* dy, int32_t n, int32_t h, in
                                     void* stream) {
     if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c) || h % 2 || w % 2)
         return nn_fail(LBM_E_INVALID, "avgpool2_backward: bad arguments");
+    RowShape rows;
     dim3 grid;
-    if (aligned16(dy) && aligned16(dx) && row_grid(n, h, w, c, &grid))
+    if (aligned16(dy) && aligned16(dx) && row_grid(n, h, w, c, &rows, &grid))
         hipLaunchKernelGGL(pool_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, (const uint16_t*)nullptr,
-                           (const uint16_t*)nullptr, dx, (uint32_t)h, (uint32_t)w, (uint32_t)c, 0u, 0u);
+                           (const uint16_t*)nullptr, dx, rows, 0u, 0u);
     else
         hipLaunchKernelGGL(avgpool2_backward_kernel, dim3(grid1((size_t)n * h * w * c)), dim3(256), 0,
                            (hipStream_t)stream, dy, dx, n, h, w, c);
@@ -260,23 +270,25 @@ lbm_status lbm_nn_avgpool2_backward(const uint16_t* dy, int32_t n, int32_t h, in
 lbm_status lbm_nn_avgpool2_backward_add(const uint16_t* dy, int32_t n, int32_t h, int32_t w, int32_t c,
                                         const uint16_t* add, int32_t ca, int32_t aoff, const uint16_t* mask,
                                         uint16_t* dx, void* stream) {
+    RowShape rows;
     dim3 grid;
     if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c) || h % 2 || w % 2 ||
         (add && (!pos(ca) || ca % 8 || aoff < 0 || aoff % 8 || (int64_t)aoff + c > ca)) || !aligned16(dy) ||
-        !aligned16(dx) || !aligned16(add) || !aligned16(mask) || !row_grid(n, h, w, c, &grid))
+        !aligned16(dx) || !aligned16(add) || !aligned16(mask) || !row_grid(n, h, w, c, &rows, &grid))
         return nn_fail(LBM_E_INVALID, "avgpool2_backward_add: bad arguments");
-    hipLaunchKernelGGL(pool_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, add, mask, dx, (uint32_t)h,
-                       (uint32_t)w, (uint32_t)c, (uint32_t)ca, (uint32_t)aoff);
+    hipLaunchKernelGGL(pool_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, add, mask, dx, rows,
+                       (uint32_t)ca, (uint32_t)aoff);
     return launched("avgpool2_backward_add");
 }
 
 lbm_status lbm_nn_upsample2(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t c, uint16_t* y,
                             void* stream) {
     if (!x || !y || !pos(n) || !pos(h) || !pos(w) || !pos(c)) return nn_fail(LBM_E_INVALID, "upsample2: bad arguments");
+    RowShape rows;
     dim3 grid;
-    if (aligned16(x) && aligned16(y) && row_grid(n, 2 * (int64_t)h, 2 * (int64_t)w, c, &grid))
+    if (aligned16(x) && aligned16(y) && row_grid(n, 2 * (int64_t)h, 2 * (int64_t)w, c, &rows, &grid))
         hipLaunchKernelGGL(up_concat_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, (const uint16_t*)nullptr, y,
-                           2u * h, 2u * w, (uint32_t)c, 0u);
+                           rows, (uint32_t)c, 0u);
     else
         hipLaunchKernelGGL(upsample2_kernel, dim3(grid1((size_t)n * 4 * h * w * c)), dim3(256), 0, (hipStream_t)stream,
                            x, y, n, h, w, c);
@@ -285,12 +297,13 @@ lbm_status lbm_nn_upsample2(const uint16_t* x, int32_t n, int32_t h, int32_t w, 
 
 lbm_status lbm_nn_upsample2_concat(const uint16_t* x, int32_t n, int32_t h, int32_t w, int32_t cx, const uint16_t* skip,
                                    int32_t cs, uint16_t* y, void* stream) {
+    RowShape rows;
     dim3 grid;
     if (!x || !skip || !y || !pos(n) || !pos(h) || !pos(w) || !pos(cx) || !pos(cs) || cx % 8 || cs % 8 ||
         !aligned16(x) || !aligned16(skip) || !aligned16(y) ||
-        !row_grid(n, 2 * (int64_t)h, 2 * (int64_t)w, (int64_t)cx + cs, &grid))
+        !row_grid(n, 2 * (int64_t)h, 2 * (int64_t)w, (int64_t)cx + cs, &rows, &grid))
         return nn_fail(LBM_E_INVALID, "upsample2_concat: bad arguments");
-    hipLaunchKernelGGL(up_concat_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, skip, y, 2u * h, 2u * w,
+    hipLaunchKernelGGL(up_concat_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, skip, y, rows,
                        (uint32_t)cx, (uint32_t)cs);
     return launched("upsample2_concat");
 }
@@ -299,10 +312,11 @@ lbm_status lbm_nn_upsample2_backward(const uint16_t* dy, int32_t n, int32_t h, i
                                      void* stream) {
     if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c))
         return nn_fail(LBM_E_INVALID, "upsample2_backward: bad arguments");
+    RowShape rows;
     dim3 grid;
-    if (aligned16(dy) && aligned16(dx) && row_grid(n, h, w, c, &grid))
+    if (aligned16(dy) && aligned16(dx) && row_grid(n, h, w, c, &rows, &grid))
         hipLaunchKernelGGL(up_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, (const uint16_t*)nullptr,
-                           dx, (uint32_t)h, (uint32_t)w, (uint32_t)c, (uint32_t)c);
+                           dx, rows, (uint32_t)c);
     else
         hipLaunchKernelGGL(upsample2_backward_kernel, dim3(grid1((size_t)n * h * w * c)), dim3(256), 0,
                            (hipStream_t)stream, dy, dx, n, h, w, c);
@@ -311,12 +325,12 @@ lbm_status lbm_nn_upsample2_backward(const uint16_t* dy, int32_t n, int32_t h, i
 
 lbm_status lbm_nn_upsample2_concat_backward(const uint16_t* dy, int32_t n, int32_t h, int32_t w, int32_t c, int32_t cd,
                                             const uint16_t* mask, uint16_t* dx, void* stream) {
+    RowShape rows;
     dim3 grid;
     if (!dy || !dx || !pos(n) || !pos(h) || !pos(w) || !pos(c) || cd < c || cd % 8 || !aligned16(dy) ||
-        !aligned16(dx) || !aligned16(mask) || !row_grid(n, h, w, c, &grid))
+        !aligned16(dx) || !aligned16(mask) || !row_grid(n, h, w, c, &rows, &grid))
         return nn_fail(LBM_E_INVALID, "upsample2_concat_backward: bad arguments");
-    hipLaunchKernelGGL(up_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, mask, dx, (uint32_t)h,
-                       (uint32_t)w, (uint32_t)c, (uint32_t)cd);
+    hipLaunchKernelGGL(up_backward_kernel, grid, dim3(256), 0, (hipStream_t)stream, dy, mask, dx, rows, (uint32_t)cd);
     return launched("upsample2_concat_backward");
 }
 

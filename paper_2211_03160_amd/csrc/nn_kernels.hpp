@@ -624,9 +624,12 @@ __global__ __launch_bounds__(256) void sum_chunks_kernel(SumChunksArgs a) {
 
 // ------------------------------------------------- layers without products
 // Memory-bound passes over NHWC tensors.  A thread takes eight channels (16
-// bytes) of one pixel; an image row takes a run of blocks, so the position in
-// it costs one 32-bit division.  The element-per-thread kernels (below) spend
-// their time on four 64-bit divisions per value.  In one gradient of the 257^2
+// bytes) of one pixel of the output, in its order in memory, so blocks are
+// full whatever the image's width (a block per run of an image row left most
+// threads idle on narrow ones: pooling 4 images of 200000 x 2, 8 channels, 147
+// us, 9 now); row and column come from two multiplications.  The
+// element-per-thread kernels (below) spend their time on four 64-bit
+// divisions per value.  In one gradient of the 257^2
 // network (batch 16) the upsampling, concatenation, pooling and ReLU passes,
 // forward and backward, took 670 us in 41 launches; joined they take 115 us in
 // 12, and the ReLU masks of the others ride in the convolutions' stores.
@@ -649,79 +652,89 @@ __device__ __forceinline__ Vec8 relu_mask(Vec8 x, Vec8 m) {
     }
     return x;
 }
-// this thread's place in output row blockIdx.x = image * h + i: pixel j, channel group k of c8
+// division of e < 2^31 by d (Granlund and Montgomery, 1994): with s = ceil(log2
+// d) and m = ceil(2^(31 + s) / d) < 2^32, m d exceeds 2^(31 + s) by less than
+// 2^s, so e m / 2^(31 + s) exceeds e / d by less than 1 / d
+struct Div31 {
+    uint32_t m, s;
+    __device__ uint32_t of(uint32_t e) const { return (uint32_t)((uint64_t)e * m >> s); }
+};
+// the output of a pass: `items` groups of eight channels, c8 per pixel, w pixels per row
+struct RowShape {
+    uint32_t items, c8, w;
+    Div31 by_c8, by_w;
+};
+// this thread's item e: channel group k of pixel j in row r = image * height + i
 struct RowPlace {
-    uint32_t b, i, j, k;
+    uint32_t e, k, j, r;
     bool in;
-    __device__ RowPlace(uint32_t h, uint32_t w, uint32_t c8) {
-        const uint32_t e = blockIdx.y * 256 + threadIdx.x;
-        b = blockIdx.x / h;
-        i = blockIdx.x - b * h;
-        j = e / c8;
-        k = e - j * c8;
-        in = j < w;
+    __device__ explicit RowPlace(const RowShape& a) {
+        e = blockIdx.x * 256 + threadIdx.x;
+        in = e < a.items;
+        const uint32_t q = a.by_c8.of(e);
+        k = e - q * a.c8;
+        r = a.by_w.of(q);
+        j = q - r * a.w;
     }
 };
 
 // x [n][h/2][w/2][cx] nearest-upsampled beside skip [n][h][w][cs] -> y [n][h][w][cx + cs]
 __global__ __launch_bounds__(256) void up_concat_kernel(const uint16_t* x, const uint16_t* skip, uint16_t* y,
-                                                        uint32_t h, uint32_t w, uint32_t cx, uint32_t cs) {
-    const RowPlace p(h, w, (cx + cs) / 8);
+                                                        RowShape a, uint32_t cx, uint32_t cs) {
+    const RowPlace p(a);
     if (!p.in) return;
-    const size_t q = ((size_t)p.b * h + p.i) * w + p.j, k = (size_t)p.k * 8;
-    const size_t low = ((size_t)p.b * (h / 2) + p.i / 2) * (w / 2) + p.j / 2;
-    store8(y + q * (cx + cs) + k, k < cx ? load8(x + low * cx + k) : load8(skip + q * cs + (k - cx)));
+    const size_t k = (size_t)p.k * 8, low = (size_t)(p.r / 2) * (a.w / 2) + p.j / 2, q = (size_t)p.r * a.w + p.j;
+    store8(y + (size_t)p.e * 8, k < cx ? load8(x + low * cx + k) : load8(skip + q * cs + (k - cx)));
 }
 
 // gradient of the upsampled part: dx [n][h][w][c] = sums of the 2x2 blocks of
 // channels 0 .. c - 1 of dy [n][2h][2w][cd], where mask (null: everywhere) is positive
 __global__ __launch_bounds__(256) void up_backward_kernel(const uint16_t* dy, const uint16_t* mask, uint16_t* dx,
-                                                          uint32_t h, uint32_t w, uint32_t c, uint32_t cd) {
-    const RowPlace p(h, w, c / 8);
+                                                          RowShape a, uint32_t cd) {
+    const RowPlace p(a);
     if (!p.in) return;
-    const size_t k = (size_t)p.k * 8, q = ((size_t)p.b * h + p.i) * w + p.j, row = (size_t)2 * w * cd;
-    const uint16_t* s = dy + (((size_t)p.b * 2 * h + 2 * p.i) * 2 * w + 2 * p.j) * cd + k;
+    const size_t row = (size_t)2 * a.w * cd;
+    const uint16_t* s = dy + 2 * p.r * row + (size_t)2 * p.j * cd + (size_t)p.k * 8;
     const Vec8 s0 = load8(s), s1 = load8(s + cd), s2 = load8(s + row), s3 = load8(s + row + cd);
     Vec8 o{v4u{0u, 0u, 0u, 0u}};
 #pragma unroll
     for (int j = 0; j < 8; ++j) o.set(j, s0.get(j) + s1.get(j) + s2.get(j) + s3.get(j));
-    if (mask) o = relu_mask(o, load8(mask + q * c + k));
-    store8(dx + q * c + k, o);
+    if (mask) o = relu_mask(o, load8(mask + (size_t)p.e * 8));
+    store8(dx + (size_t)p.e * 8, o);
 }
 
-// x [n][h][w][c] -> y [n][h/2][w/2][c], 2x2 means; h, w of y
-__global__ __launch_bounds__(256) void pool_kernel(const uint16_t* x, uint16_t* y, uint32_t h, uint32_t w, uint32_t c) {
-    const RowPlace p(h, w, c / 8);
+// x [n][2h][2w][c] -> y [n][h][w][c], 2x2 means
+__global__ __launch_bounds__(256) void pool_kernel(const uint16_t* x, uint16_t* y, RowShape a) {
+    const RowPlace p(a);
     if (!p.in) return;
-    const size_t k = (size_t)p.k * 8, row = (size_t)2 * w * c;
-    const uint16_t* s = x + (((size_t)p.b * 2 * h + 2 * p.i) * 2 * w + 2 * p.j) * c + k;
+    const size_t c = (size_t)a.c8 * 8, row = 2 * a.w * c;
+    const uint16_t* s = x + 2 * p.r * row + 2 * p.j * c + (size_t)p.k * 8;
     const Vec8 s0 = load8(s), s1 = load8(s + c), s2 = load8(s + row), s3 = load8(s + row + c);
     Vec8 o{v4u{0u, 0u, 0u, 0u}};
 #pragma unroll
     for (int j = 0; j < 8; ++j) o.set(j, 0.25f * (s0.get(j) + s1.get(j) + s2.get(j) + s3.get(j)));
-    store8(y + (((size_t)p.b * h + p.i) * w + p.j) * c + k, o);
+    store8(y + (size_t)p.e * 8, o);
 }
 
 // gradient of the pooling: dx [n][h][w][c] = dy [n][h/2][w/2][c] / 4, plus
 // channels ao .. ao + c - 1 of add [n][h][w][ca] (null: nothing), where mask
 // (null: everywhere) is positive; each sum rounded to BF16 as it is formed
 __global__ __launch_bounds__(256) void pool_backward_kernel(const uint16_t* dy, const uint16_t* add, const uint16_t* mask,
-                                                            uint16_t* dx, uint32_t h, uint32_t w, uint32_t c,
-                                                            uint32_t ca, uint32_t ao) {
-    const RowPlace p(h, w, c / 8);
+                                                            uint16_t* dx, RowShape a, uint32_t ca, uint32_t ao) {
+    const RowPlace p(a);
     if (!p.in) return;
-    const size_t k = (size_t)p.k * 8, q = ((size_t)p.b * h + p.i) * w + p.j;
-    const Vec8 s = load8(dy + (((size_t)p.b * (h / 2) + p.i / 2) * (w / 2) + p.j / 2) * c + k);
+    const size_t k = (size_t)p.k * 8, low = (size_t)(p.r / 2) * (a.w / 2) + p.j / 2;
+    const Vec8 s = load8(dy + low * a.c8 * 8 + k);
     Vec8 o{v4u{0u, 0u, 0u, 0u}};
 #pragma unroll
     for (int j = 0; j < 8; ++j) o.set(j, 0.25f * s.get(j));
     if (add) {
-        const Vec8 d = load8(add + q * ca + ao + k);
+        const Vec8 d = load8(add + ((size_t)p.r * a.w + p.j) * ca + ao + k);
 #pragma unroll
         for (int j = 0; j < 8; ++j) o.set(j, o.get(j) + d.get(j));
     }
-    if (mask) o = relu_mask(o, load8(mask + q * c + k));
-    store8(dx + q * c + k, o);
+    if (mask) o = relu_mask(o, load8(mask + (size_t)p.e * 8));
+    store8(dx + (size_t)p.e * 8, o);
 }
 
 // dst[p][doff + k] (+)= src[p][soff + k] for k < cc; c8 = cc / 8

@@ -75,3 +75,37 @@ def test_convolution_output_and_mask_off_8_byte_addresses(ci, co, skew):
     nn._check(nn.lib().lbm_nn_conv3x3_masked(nn._p(x), n, h, w, ci, nn._p(wt), nn._p(m), co, nn._p(y), nn._s()))
     assert torch.equal(y, want)
     assert (flat[:skew] == 0x7abc).all() and (flat[skew + size:] == 0x7abc).all()
+
+
+# narrow images (many rows per block), rows of odd lengths, one channel group,
+# image rows longer than 65535 blocks of 256 groups (the concatenation), and
+# more rows than one launch can hold blocks for
+@pytest.mark.parametrize("n,h,w,c,cs", [(7, 50, 1, 8, 8), (1, 1, 129, 24, 16), (300, 1, 1, 40, 8), (5, 13, 17, 8, 48),
+                                        (1, 1, 65600, 512, 512), ((1 << 23) + 5, 1, 1, 8, 8)])
+def test_row_passes_of_any_shape(n, h, w, c, cs):
+    """Copies and sums of four BF16 values: the same bits as torch."""
+    import torch
+    from paper_2211_03160_amd import nn
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + w)
+    val = lambda *s: (torch.randint(-64, 65, s, generator=g, device="cuda").to(torch.bfloat16) / 16)  # noqa: E731
+    raw = lambda t: t.contiguous().view(torch.int16)  # noqa: E731
+    up = lambda t: t[:, :, None, :, None].expand(n, h, 2, w, 2, t.shape[-1]).reshape(n, 2 * h, 2 * w, -1)  # noqa: E731
+    quad = lambda t: t.reshape(n, h, 2, w, 2, t.shape[-1])  # noqa: E731
+    x, skip = val(n, h, w, c), val(n, 2 * h, 2 * w, cs)
+    cat = torch.cat([up(x), skip], -1)
+    assert torch.equal(nn.upsample2(raw(x)), raw(up(x)))
+    assert torch.equal(nn.upsample2_concat(raw(x), raw(skip)), raw(cat))
+    q = quad(cat)
+    four = lambda t: ((t[:, :, 0, :, 0].float() + t[:, :, 0, :, 1].float())  # noqa: E731
+                      + t[:, :, 1, :, 0].float()) + t[:, :, 1, :, 1].float()
+    assert torch.equal(nn.avgpool2(raw(cat)), raw((0.25 * four(q)).to(torch.bfloat16)))
+    s = four(q[..., :c]).to(torch.bfloat16)
+    assert torch.equal(nn.upsample2_concat_backward(raw(cat), raw(x)), raw(torch.where(x > 0, s, 0)))
+    assert torch.equal(nn.upsample2_backward(raw(skip)), raw(four(quad(skip)).to(torch.bfloat16)))
+    y = val(n, 2 * h, 2 * w, cs)
+    dlow = val(n, h, w, cs)
+    part = (0.25 * up(dlow).float()).to(torch.bfloat16)
+    assert torch.equal(nn.avgpool2_backward(raw(dlow)), raw(part))
+    add = (part.float() + cat[..., c:].float()).to(torch.bfloat16)
+    assert torch.equal(nn.avgpool2_backward_add(raw(dlow), raw(cat), raw(y)), raw(torch.where(y > 0, add, 0)))
