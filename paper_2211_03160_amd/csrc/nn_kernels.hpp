@@ -370,14 +370,26 @@ __global__ __launch_bounds__(256) void wflip_kernel(FlipArgs a) {
         if (i0 + y + k < ci && o0 + x < co) dst[(size_t)(i0 + y + k) * co + o0 + x] = t[x][y + k];
 }
 
+// division of e < 2^31 by d (Granlund and Montgomery, 1994): with s = ceil(log2
+// d) and m = ceil(2^(31 + s) / d) < 2^32, m d exceeds 2^(31 + s) by less than
+// 2^s, so e m / 2^(31 + s) exceeds e / d by less than 1 / d
+struct Div31 {
+    uint32_t m, s;
+    __device__ uint32_t of(uint32_t e) const { return (uint32_t)((uint64_t)e * m >> s); }
+};
+
 struct WGradArgs {
     const uint16_t* x;   // [n][h][w][cin]
     const uint16_t* dz;  // [n][h][w][cout]
     float* partial;      // [chunks][9][cout][cin]
     float* bias;         // [chunks][cout], or null
     int32_t n, h, w, cin, cout;
-    uint32_t tiles_x, tiles_y, tiles;  // pixel tiles per image row and column, of all images
+    uint32_t tiles_x, tiles_y, tiles;  // pixel tiles per row and per image column (not stacked), and in all
     uint32_t per, chunks;              // tiles per chunk, chunks
+    // stacked: images beside each other, columns and rows of the stack, columns
+    // from image to image (2^31 - 1 with one across), and division by that and by h + 1
+    uint32_t across, cols, rows, col_pitch;
+    Div31 by_col_pitch, by_pitch;
 };
 
 // dW[tap][co][ci] = sum_p dz[p][co] x[p shifted by tap][ci] and db[co] =
@@ -389,7 +401,10 @@ struct WGradArgs {
 // transposing read: of the 16 lanes of a group, lanes 4r .. 4r + 3 point at
 // the 16 channels of pixel r, and lane i receives channel i of the four
 // pixels.  A tap is then an offset of whole pixels.  Pixels outside the image
-// are zeros in both tiles.  The block's WCO x WCI wavefronts tile the
+// are zeros in both tiles.  Images of a few rows are stacked, and narrow ones
+// set beside each other too, with a row and a column of zeros between them, so
+// that they fill tiles (Stacked; 4096 images of 1 x 1, 256 -> 256 channels:
+// 60 us, 320 with tiles of each image's own; 16 of 2 x 2 19 and 37).  The block's WCO x WCI wavefronts tile the
 // channels, WK of them split the K steps and add their sums at the end; the
 // chunks (runs of tiles) are summed by sum_chunks_kernel.  The bias gradient
 // is one more MFMA against ones.
@@ -411,7 +426,7 @@ __device__ __forceinline__ v4u lds_transposed(const unsigned char* p, const unsi
 }
 
 constexpr int kWgTileH = 16;  // rows of a pixel tile (four K steps)
-template <int WCO, int WCI, int WK, int KX>
+template <int WCO, int WCI, int WK, int KX, bool Stacked>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void wgrad_kernel(WGradArgs a) {
     static_assert(WCO * WCI * WK == 4, "four wavefronts");
@@ -450,30 +465,63 @@ void wgrad_kernel(WGradArgs a) {
 
     for (uint32_t k = threadIdx.x; k < kZeroBytes / 16; k += 256) *(v4u*)(lds + kZeroAt + k * 16) = v4u{0u, 0u, 0u, 0u};
 
+    // a tile: its first column, the image row of its first pixel row (not
+    // stacked: the image) and the row in it, and that row's place in the stack
+    struct Tile {
+        uint32_t x0, img, y0, v0;
+    };
+    const uint32_t h = (uint32_t)a.h, w = (uint32_t)a.w, n = (uint32_t)a.n, pitch = h + 1, cpitch = a.col_pitch;
+    // Stacked: the image, row and column of place (u, c) from image row r0 on
+    struct Pixel {
+        uint32_t img, y, x;
+        bool in;
+    };
+    auto pixel = [&](uint32_t r0, uint32_t u, uint32_t c) __attribute__((always_inline)) {
+        const uint32_t d = a.by_pitch.of(u), g = a.by_col_pitch.of(c);
+        Pixel q{(r0 + d) * a.across + g, u - d * pitch, c - g * cpitch, false};
+        q.in = q.y < h && q.x < w && g < a.across && q.img < n;
+        return q;
+    };
     v4u dv[PD], xv[PX];
-    uint32_t tx = 0, ty = 0;
     auto load = [&](uint32_t t) __attribute__((always_inline)) {
-        const uint32_t img = t / (a.tiles_x * a.tiles_y), r2 = t - img * (a.tiles_x * a.tiles_y);
-        const int32_t y0 = (int32_t)(r2 / a.tiles_x) * TH, x0 = (int32_t)(r2 % a.tiles_x) * TW;
-        const size_t base = (size_t)img * a.h * a.w;
+        Tile at;
+        at.v0 = t / a.tiles_x * TH;
+        at.x0 = t % a.tiles_x * TW;
+        at.img = Stacked ? at.v0 / pitch : t / (a.tiles_x * a.tiles_y);
+        at.y0 = at.v0 - at.img * (Stacked ? pitch : a.tiles_y * TH);
+        const size_t base = Stacked ? 0 : (size_t)at.img * h * w;
 #pragma unroll
         for (int p = 0; p < PD; ++p) {
             const int e = p * 256 + (int)threadIdx.x, px = e / (COB / 8), k = e % (COB / 8);
-            const int32_t y = y0 + px / TW, x = x0 + px % TW, ch = (int32_t)cb * COB + k * 8;
+            const uint32_t ch = cb * COB + k * 8, y = at.y0 + px / TW, x = at.x0 + px % TW;
+            size_t from = base + (size_t)y * w + x;
+            bool in = y < h && x < w;
+            if constexpr (Stacked) {
+                const Pixel q = pixel(at.img, y, x);
+                from = ((size_t)q.img * h + q.y) * w + q.x;
+                in = q.in;
+            }
             dv[p] = v4u{0u, 0u, 0u, 0u};
-            if (e < ND && y < a.h && x < a.w && ch < a.cout)
-                dv[p] = *(const v4u*)(a.dz + (base + (size_t)y * a.w + x) * a.cout + ch);
+            if (e < ND && in && ch < (uint32_t)a.cout) dv[p] = *(const v4u*)(a.dz + from * a.cout + ch);
         }
 #pragma unroll
         for (int p = 0; p < PX; ++p) {
             const int e = p * 256 + (int)threadIdx.x, px = e / (CIB / 8), k = e % (CIB / 8);
-            const int32_t y = y0 - 1 + px / (TW + 2), x = x0 - 1 + px % (TW + 2), ch = (int32_t)ib * CIB + k * 8;
+            // row and column -1 wrap and lie outside too
+            const uint32_t ch = ib * CIB + k * 8, y = at.y0 + px / (TW + 2) - 1, x = at.x0 + px % (TW + 2) - 1;
+            size_t from = base + (size_t)y * w + x;
+            bool in = y < h && x < w;
+            if constexpr (Stacked) {
+                const Pixel q = pixel(at.img - 1, y + pitch, x);  // from the zeros above image row at.img on
+                from = ((size_t)q.img * h + q.y) * w + q.x;
+                in = x + 1 > 0 && q.in;
+            }
             xv[p] = v4u{0u, 0u, 0u, 0u};
-            if (e < NX && y >= 0 && y < a.h && x >= 0 && x < a.w && ch < a.cin)
-                xv[p] = *(const v4u*)(a.x + (base + (size_t)y * a.w + x) * a.cin + ch);
+            if (e < NX && in && ch < (uint32_t)a.cin) xv[p] = *(const v4u*)(a.x + from * a.cin + ch);
         }
+        return at;
     };
-    load(t_begin);
+    Tile next = load(t_begin);
     for (uint32_t t = t_begin; t < t_end; ++t) {
         if (t > t_begin) __syncthreads();  // the previous tile has been read
 #pragma unroll
@@ -487,22 +535,23 @@ void wgrad_kernel(WGradArgs a) {
             if (NX % 256 == 0 || e < NX) *(v4u*)(lds + kXAt + e / (CIB / 8) * SX + e % (CIB / 8) * 16) = xv[p];
         }
         __syncthreads();
-        const uint32_t r2 = t % (a.tiles_x * a.tiles_y);
-        ty = r2 / a.tiles_x;
-        tx = r2 % a.tiles_x;
-        if (t + 1 < t_end) load(t + 1);
+        const Tile at = next;
+        if (t + 1 < t_end) next = load(t + 1);
         for (uint32_t ks = wk; ks < KX * (TH / 4); ks += WK) {
             const uint32_t kx = ks % KX * 8, ky = ks / KX * 4;
-            if (ty * TH + ky >= (uint32_t)a.h || tx * TW + kx >= (uint32_t)a.w) continue;  // all outside
+            const bool rows_in = Stacked ? at.v0 + ky < a.rows : at.y0 + ky < h;
+            if (!rows_in || at.x0 + kx >= (Stacked ? a.cols : w)) continue;  // all outside
             const unsigned char* pd = lds + ((ky + kg) * TW + kx + (i >> 2)) * SD + wco * 64 + (i & 3) * 8;
             // this lane's pixels of the K step, four apart.  Outside the image
             // dz is 0, but the x beside it may lie inside, and 0 times an
             // infinity must not reach a tap that does not use it: there a
             // lane points at zeros.
             const unsigned char* px = lds + kXAt + ((ky + kg) * (TW + 2) + kx + (i >> 2)) * SX + wci * 64 + (i & 3) * 8;
-            const uint32_t in = ty * TH + ky + kg < (uint32_t)a.h ? (uint32_t)a.w - tx * TW - kx : 0u;
-            const unsigned char* px4 = (i >> 2) + 4 < in ? px + 4 * SX : lds + kZeroAt;
-            px = (i >> 2) < in ? px : lds + kZeroAt;
+            const uint32_t y = at.y0 + ky + kg, x = at.x0 + kx + (i >> 2);
+            const bool in = Stacked ? pixel(at.img, y, x).in : y < h && x < w;
+            const bool in4 = Stacked ? pixel(at.img, y, x + 4).in : y < h && x + 4 < w;
+            const unsigned char* px4 = in4 ? px + 4 * SX : lds + kZeroAt;
+            px = in ? px : lds + kZeroAt;
             v4u av[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) av[u] = lds_transposed(pd + u * 32, pd + u * 32 + 4 * SD);
@@ -652,13 +701,6 @@ __device__ __forceinline__ Vec8 relu_mask(Vec8 x, Vec8 m) {
     }
     return x;
 }
-// division of e < 2^31 by d (Granlund and Montgomery, 1994): with s = ceil(log2
-// d) and m = ceil(2^(31 + s) / d) < 2^32, m d exceeds 2^(31 + s) by less than
-// 2^s, so e m / 2^(31 + s) exceeds e / d by less than 1 / d
-struct Div31 {
-    uint32_t m, s;
-    __device__ uint32_t of(uint32_t e) const { return (uint32_t)((uint64_t)e * m >> s); }
-};
 // the output of a pass: `items` groups of eight channels, c8 per pixel, w pixels per row
 struct RowShape {
     uint32_t items, c8, w;

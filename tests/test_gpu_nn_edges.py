@@ -109,3 +109,19 @@ def test_row_passes_of_any_shape(n, h, w, c, cs):
     assert torch.equal(nn.avgpool2_backward(raw(dlow)), raw(part))
     add = (part.float() + cat[..., c:].float()).to(torch.bfloat16)
     assert torch.equal(nn.avgpool2_backward_add(raw(dlow), raw(cat), raw(y)), raw(torch.where(y > 0, add, 0)))
+
+
+# images lower than a tile of 16 rows, one row off it, and tall ones; narrow
+# and one off 8 and 16 columns; tiles that hold many images and parts of two
+@pytest.mark.parametrize("n,h,w", [(70, 1, 1), (16, 2, 2), (33, 1, 9), (9, 3, 5), (5, 15, 9), (4, 16, 17), (3, 31, 7)])
+@pytest.mark.parametrize("ci,co", [(16, 16), (64, 32), (32, 80), (128, 64)])
+def test_wgrad_of_many_small_images(n, h, w, ci, co):
+    rng = np.random.default_rng(n * h + w + ci)
+    x, dz = _bf(rng.standard_normal((n, h, w, ci))), _bf(rng.standard_normal((n, h, w, co)))
+    zero = np.zeros((3, 3, ci, co))
+    _, ref, bref = R.conv3x3_backward(x, zero, dz)
+    _, scale, bscale = R.conv3x3_backward(np.abs(x), zero, np.abs(dz))
+    for chunks in (1, 4, 50):
+        got, bias = _wgrad(_dev_bf16(x), _dev_bf16(dz), co, chunks)
+        assert np.all(np.abs(got - ref) <= 1e-5 * scale + 1e-6)
+        assert np.all(np.abs(bias - bref) <= 1e-5 * bscale + 1e-6)
