@@ -915,6 +915,7 @@ template <class St> struct StreamArgs {
     uint32_t strips, segs;    // strips across x, row segments of a strip
     uint32_t seg_rows;        // rows per strip segment
     uint32_t first_rows;      // rows of the first one
+    uint32_t walls_first;     // the order of the units: see unit_pos
     uint32_t units;           // strips x segments, one per wavefront
     uint32_t blocks_per_xcd;
 };
@@ -946,17 +947,27 @@ template <class St, int NS> constexpr bool stream_in_step() {
     return std::is_same_v<St, StF32> && NS == 5;
 }
 
-// The strip and the row segment of a work unit.  Units follow the segments,
-// strip by strip, except that the two strips at walls in x come first in
-// each group of kUnitGroup segments: wall rules make a strip's sweep 1.6 times
-// as long, and so the wavefronts of a block, and what a launch ends on, take
-// alike time.  A group, not the whole grid: every XCD then has its share.
+// Whether the two strips at walls in x come first in each group of kUnitGroup
+// segments: wall rules make a strip's sweep 1.6 times as long, and so the
+// wavefronts of a block, and what a launch ends on, take alike time.  A
+// group, not the whole grid: every XCD then has its share.  Launches of few
+// steps with FP32 populations are bound by the traffic instead and keep the
+// plain order, in which a row of strips is stored together.  us per step,
+// plain / walls first, 6145 x 5000: FP32 at two steps 440 / 446, at three 301 /
+// 308, at four 214 / 210; FP16-f+FP32-g at two 310 / 316; FP64 810 / 790; BF16
+// at four 174 / 159 (40 rows).  Batches of two 2049^2: FP32 at two 125 / 130.
 constexpr uint32_t kUnitGroup = 16;
+template <class St, int NS> constexpr bool stream_walls_first() {
+    return sizeof(typename St::TG) != 4 || NS > 3;
+}
+
+// The strip and the row segment of a work unit.  Units follow the segments,
+// strip by strip, or with the strips at walls first (above).
 struct UnitPos {
     uint32_t strip, seg;
 };
-__device__ __forceinline__ UnitPos unit_pos(uint32_t unit, uint32_t strips, uint32_t segs, bool walls_x) {
-    if (!walls_x || strips < 3) return {unit % strips, unit / strips};
+__device__ __forceinline__ UnitPos unit_pos(uint32_t unit, uint32_t strips, uint32_t segs, bool walls_first) {
+    if (!walls_first) return {unit % strips, unit / strips};
     const uint32_t seg0 = unit / (strips * kUnitGroup) * kUnitGroup;
     const uint32_t here = min(kUnitGroup, segs - seg0), r = unit - seg0 * strips;
     if (r < 2 * here) return {r < here ? 0u : strips - 1, seg0 + (r < here ? r : r - here)};
@@ -976,7 +987,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
     const Geometry& g = a.geo;
     const int lane = (int)(threadIdx.x & 63);
     bool bad = false;
-    const UnitPos at = unit_pos(unit, a.strips, a.segs, !g.periodic[0]);
+    const UnitPos at = unit_pos(unit, a.strips, a.segs, a.walls_first);
     const int32_t x0 = (int32_t)(at.strip * W);
     const int32_t y0 = at.seg ? (int32_t)(a.first_rows + (at.seg - 1) * a.seg_rows) : 0;
     const int32_t rows = min((int32_t)(at.seg ? a.seg_rows : a.first_rows), (int32_t)g.ny - y0);

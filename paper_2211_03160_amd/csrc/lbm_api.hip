@@ -658,6 +658,7 @@ template <class St, int NS, int D> void stream_launches(lbm_ctx* c, int64_t k) {
     a.c = make_coef<typename St::R>(c);
     a.strips = (c->geo.nx + W - 1) / W;
     a.seg_rows = stream_seg_rows<St, NS>((uint64_t)a.strips * c->geo.ny, c->cus);
+    a.walls_first = stream_walls_first<St, NS>() && !c->geo.periodic[0] && a.strips >= 3;
     // The segments at walls in y get what is left over, in two halves: with
     // wall rules a row takes 1.6 times as long, and the last segment's units
     // are what the launch ends on.
