@@ -629,10 +629,15 @@ bool streamable3(const lbm_ctx* c) {
 // 56 / 72 rows: 4097^2 (rule 35) 150 / 149 / 152 / 145 / 158, 6145x5000 (47)
 // 164 / 168 / 172 / 170 / 168, 12000x6000 (72) 168 / 174 / 180 / 182 / 182,
 // 8193^2 (70) 168 / 172 / 179 / 178 / 180.
-// The other modes take one length, measured on 4097^2 and 8193^2: FP16 at
-// three 133 / 150 / 147 and 173 / 178 / 179 at 32 / 48 / 56 rows; BF16 at four
-// 155 / 150 / 163 and 182 / 193 / 195, FP16-f+FP32-g at four 144 / 139 / 152
-// and 167 / 177 / 178.  FP32 at three 117 / 111 / 107 / 97 at 16 / 24 / 32 / 64
+// 16-bit storage at three and four steps follows it from 16 rows on, times a
+// factor (their wavefronts do not run in step, and end at different times),
+// up to the length that is best on 8193^2.  us per step at 16 / 24 / 32 / 40 /
+// 48 / 56 rows: FP16 at three 1025^2 (rule 16) 18.7 / 19.5 / 24.7 / 29.6 / 35.1 /
+// 39.9, 2999^2 (24) 61.6 / 58.8 / 58.5 / 65.0 / 68.0 / 69.5, 6145x5000 (44) 184 /
+// 179 / 178 / 177 / 173 / 180; BF16 at four 2049x1537 (16) 27.3 / 31.0 / 29.8 /
+// 30.0 / 42.3 / 36.6, 2999^2 (32) 60.0 / 54.2 / 58.8 / 59.4 / 62.6 / 68.8, 4097^2
+// (44) 108 / 103 / 104 / 103 / 108 / 100 (95 at 44).
+// The other modes take one length: FP32 at three 117 / 111 / 107 / 97 at 16 / 24 / 32 / 64
 // on 8193^2, at four 149 / 145 / 138 at 16 / 24 / 32; FP64 at two 39 / 37 / 36 /
 // 36 at 16 / 24 / 32 / 64.
 template <class St, int NS> uint32_t stream_seg_rows(uint64_t strip_rows, int cus) {
@@ -644,8 +649,12 @@ template <class St, int NS> uint32_t stream_seg_rows(uint64_t strip_rows, int cu
         const double A = (double)strip_rows / (4.0 * stream_waves_per_simd<St, NS>() * std::max(cus, 1));
         return (uint32_t)std::min(72.0, std::max(24.0, std::sqrt(2.0 * (NS - 1) * A)));
     } else if constexpr (f32) return 16;
-    else if constexpr (half) return NS == 2 ? 40 : NS == 3 ? 48 : 56;
-    else return NS == 2 ? 16 : NS == 3 ? 40 : 56;  // FP16 f, FP32 g
+    else if constexpr (NS == 4 || (half && NS == 3)) {
+        const double A = (double)strip_rows / (4.0 * stream_waves_per_simd<St, NS>() * std::max(cus, 1));
+        const double r = (NS == 3 ? 1.75 : 1.5) * std::sqrt(2.0 * (NS - 1) * A);
+        return (uint32_t)std::min(NS == 3 ? 48.0 : 56.0, std::max(16.0, r)) / 4 * 4;
+    } else if constexpr (half) return 40;
+    else return NS == 2 ? 16 : 40;  // FP16 f, FP32 g
 }
 
 // k launches of the register-row kernel of NS steps each (prefetch distance
