@@ -732,14 +732,31 @@ template <class St, int RX, int RY, int KT> void tile2_launches(lbm_ctx* c, int6
     }
 }
 
+// Largest grid whose last 2 .. 4 steps, after launches of more, go through
+// tiles: 16 x 16 regions, which store little of what they compute (100 of 256
+// nodes at four steps); larger ones stream them.  us, tiles / streaming: FP32 two
+// steps 1601x1301 39 / 59, 1537x2049 105 / 101, 2500^2 201 / 191, three 51 / 65,
+// 117 / 107, 229 / 201, four 84 / 78, 144 / 118, 275 / 195; BF16 two steps
+// 2049^2 62 / 77, 2500x2200 118 / 108, three 1537x2049 80 / 79, 2500^2 166 / 126;
+// FP16 about the same; FP16-f+FP32-g two steps 1537x2049 50 / 64, 2049^2 111 / 97,
+// three 86 / 114, 126 / 120, 2800^2 231 / 218; FP64 faster in tiles at all sizes
+// (3872^2 773 / 776, 859 / 1379).
+template <class St> uint32_t tile2_most_rest(int rest) {
+    if (sizeof(typename St::R) == 8) return UINT32_MAX;
+    if (sizeof(typename St::TF) == 4) return rest == 4 ? 2000000u : 2800000u;
+    if (sizeof(typename St::TG) == 4) return 3500000u;
+    return rest == 2 ? 4800000u : 3300000u;
+}
+
 // n steps with the tile kernel: launches of K steps on RX x RY regions (KT:
-// K compiled in, or 0), the rest in one launch of fewer steps.  Leaves one
-// step over (returned) when the rest is one: the one-step kernel's.
+// K compiled in, or 0), the rest in one launch of fewer steps, or left over
+// (returned): to the streaming kernel, or one step to the one-step kernel.
 template <class St, int RX, int RY, int KT> int64_t tile2_run(lbm_ctx* c, int64_t n, int K) {
     if (n >= K) tile2_launches<St, RX, RY, KT>(c, n / K, K);
     const int rest = (int)(n % K);
-    if (rest >= 2) tile2_launches<St, 16, 16, 0>(c, 1, rest);
-    return rest == 1 ? 1 : 0;
+    if (rest < 2 || c->geo.N > tile2_most_rest<St>(rest)) return rest;
+    tile2_launches<St, 16, 16, 0>(c, 1, rest);
+    return 0;
 }
 
 // Largest grid the tile kernel steps by default.  Measured on square
