@@ -1000,6 +1000,12 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
     // and a multiply-add.
     const R tb_x = a.c.bt.axis == 0 ? base_temp(a.c.bt, ucol, 0u, 0u) : a.c.bt.tb0;
     const R tb_y = a.c.bt.axis == 1 ? a.c.bt.tbg : (R)0;
+    auto tb = [&](uint32_t yy) __attribute__((always_inline)) {
+        // FP64 in batches spills as it is and has no registers for the two
+        // (two 2049^2: 360 us a step from the start, 388 from the parts)
+        if constexpr (Report && sizeof(R) == 8) return base_temp(a.c.bt, ucol, yy, 0u);
+        else return tb_x + tb_y * (R)yy;
+    };
 
     // Rings: NI input rows, R rows of each intermediate step; the loop is
     // unrolled over U = NI iterations so that every ring index is a
@@ -1105,7 +1111,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
                 typename St::TF ef[QF];
                 typename St::TG eg[QG];
                 if (needed(NS, yj)) {
-                    const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb_x + tb_y * (R)yy, x, yy, 0u, src,
+                    const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb(yy), x, yy, 0u, src,
                                                             EncDst<St, QF, QG>{ef, eg}, fx);
                     if constexpr (Report) bad = bad || (own && !ok);
                 } else {
@@ -1122,7 +1128,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
                 static_for<0, QG>([&](auto ic) { dst.sg(decltype(ic)::value, eg[decltype(ic)::value]); });
             } else if (needed(j, yj)) {
                 const RegDst<St, QF, QG> dst{fs[j - 1][st(0)], gs[j - 1][st(0)]};
-                const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb_x + tb_y * (R)yy, x, yy, 0u, src, dst, fx);
+                const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb(yy), x, yy, 0u, src, dst, fx);
                 // an intermediate state is checked too where it is a real
                 // node's: a valid lane of step j inside the domain
                 if constexpr (Report)
@@ -1140,7 +1146,7 @@ __device__ __forceinline__ bool stream_unit(const StreamArgs<St>& a, uint32_t un
                                          gin[in(2 + D)], gin[in(1 + D)], gin[in(D)]};
             const RegDst<St, QF, QG> dst{fs[0][st(0)], gs[0][st(0)]};
             const bool own = own_col && y1 >= y0 && y1 < y0 + rows;
-            const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb_x + tb_y * (R)yy, ucol, yy, 0u, src, dst,
+            const bool ok = step_node_at<2, St, Wl>(g, a.c, nb, tb(yy), ucol, yy, 0u, src, dst,
                                                  BufFlux2{rflux, a.slot[(tp + 1) & 1], a.flux_bytes, own});
             if constexpr (Report) bad = bad || (!ok && lane >= 1 && lane <= 62 && col >= 0 && r1 >= 0);
         }
@@ -1191,8 +1197,15 @@ template <class St> struct BatchStreamArgs {
 
 // NWB bounds the wavefronts per block; a launch may use fewer (any block
 // of blockDim.x / 64 wavefronts).
+// Three steps with FP32 g need 166 registers, which would let a third
+// wavefront onto a SIMD: more strips at once than the L2 keeps lines for
+// (FP32, two 2049^2: 85 us a step with two, 91 with three).
+template <class St, int NS> constexpr int batch_most_waves() {
+    return NS == 3 && sizeof(typename St::TG) == 4 ? 2 : 8;
+}
 template <class St, int NWB, bool O32, int NS, int D>
-__global__ __launch_bounds__(64 * NWB) __attribute__((amdgpu_waves_per_eu(stream_waves_per_simd<St, NS>())))
+__global__ __launch_bounds__(64 * NWB)
+__attribute__((amdgpu_waves_per_eu(stream_waves_per_simd<St, NS>(), batch_most_waves<St, NS>())))
 void batch_stream_kernel(BatchStreamArgs<St> b) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nw = blockDim.x >> 6;
