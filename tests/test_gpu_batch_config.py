@@ -96,3 +96,18 @@ def test_launch_kind_follows_the_configuration():
     assert b.launch_steps == count
     b.set_config(tiles=1)
     assert b.launch_steps == count
+
+
+@pytest.mark.parametrize("storage,shapes", [("fp16", [(700, 700)] * 4 + [(300, 203)]), ("fp16", [(700, 700)] * 4),
+                                            ("bf16", LARGE), ("fp64", [(700, 700)] * 5)])
+def test_steps_left_over_by_tiles(storage, shapes):
+    """Every remainder of the tile launches, on either side of the two million
+    nodes from which FP16 streams three steps, launched and from graphs."""
+    b = _batch(storage, shapes)
+    _init(b)
+    for n in (1, 2, 3, 5, 6, 7):
+        b.step(n)
+    _same_as_single_steps(b, storage, shapes)
+    b.set_config(graph_steps=14)
+    b.step(31)
+    _same_as_single_steps(b, storage, shapes)
