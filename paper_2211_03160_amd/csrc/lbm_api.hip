@@ -239,6 +239,7 @@ struct lbm_ctx {
     bool view;    // a cavity owned by a batch: the batch steps and initialises it
     int32_t steps_per_launch;  // time steps per launch of lbm_step (1-5 in 2D, 1-2 in 3D)
     bool steps_set;            // the count was set by the caller: launches take exactly it
+    int two_steps_pay = -1;    // stream3_pays, once it has been asked for
     int cus;                   // compute units of the device
     bool poison;               // debug: fill the destination state with NaN before every launch
     double* sums = nullptr;    // see take_sums
@@ -808,21 +809,17 @@ template <class St> int64_t tile2_auto(lbm_ctx* c, int64_t n) {
     }
 }
 
-// Whether the 3D two-step kernel is used where the caller chose no count.
-// Small grids stay in the caches, and the two-step kernel's blocks (one tile
-// of columns each, a plane at a time) leave compute units idle, so the
-// one-step kernel wins there.  us per step in FP32, one step against two:
-// 17^3 4.0 / 6.1, 33^3 4.4 / 6.5, 49^3 5.9 / 9.1, 65^3 13.7 / 13.3, 97^3 37 /
-// 27.7.
-bool stream3_pays(const lbm_ctx* c) { return c->geo.N >= 250000u; }
-
 // z segments of the 3D two-step kernel.  Each segment repeats the first
 // step on one plane below and one above it, and its block holds a compute
 // unit's LDS for the whole segment, so a launch runs in rounds: each XCD
 // takes its share of blocks `resident` per compute unit at a time.  The
 // count chosen minimises rounds x (planes per segment + 2), the plane
 // steps of the slowest compute unit (fewer segments on a tie).
-uint32_t stream3_segments(uint32_t nz, uint32_t tiles, int cus, int resident) {
+struct Stream3Segments {
+    uint32_t segs;
+    uint64_t cost;  // plane steps
+};
+Stream3Segments stream3_segments(uint32_t nz, uint32_t tiles, int cus, int resident) {
     const uint64_t slots = (uint64_t)std::max(cus / kXcd, 1) * (uint64_t)std::max(resident, 1);
     uint32_t best = 1;
     uint64_t best_cost = UINT64_MAX;
@@ -836,7 +833,32 @@ uint32_t stream3_segments(uint32_t nz, uint32_t tiles, int cus, int resident) {
             best = segs;
         }
     }
-    return best;
+    return {best, best_cost};
+}
+
+template <class St> Stream3Segments stream3_split(const lbm_ctx* c) {
+    static const int resident = [] {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stream3_kernel<St>, kT3Threads, 0) != hipSuccess) n = 1;
+        return std::max(n, 1);
+    }();
+    const uint32_t tiles = ((c->geo.nx + kT3OutX - 1) / kT3OutX) * ((c->geo.ny + kT3OutY - 1) / kT3OutY);
+    return stream3_segments(c->geo.nz, tiles, c->cus, resident);
+}
+
+// Whether the 3D two-step kernel is used where the caller chose no count.
+// Small grids stay in the caches, where the one-step kernel takes 0.05 us per
+// thousand nodes, and the two-step kernel's blocks (one tile of columns each,
+// a plane at a time) leave compute units idle: it takes 3.8 us per plane step
+// whatever the grid.  us per step in FP32, one step against two, with
+// thousands of nodes per plane step: 49^3 6.1 / 9.1 (29), 128x512x3 8.7 / 10.0
+// (39), 62^3 12.7 / 13.2 (40), 64x64x60 12.3 / 13.0 (41), 300x300x2 8.1 / 8.0 (45),
+// 400x200x3 11.9 / 10.0 (48), 200x100x12 12.7 / 11.0 (48), 350x350x2 11.1 / 13.4
+// (31), 16x16x900 12.0 / 21.2 (23).  From 250 thousand nodes on two steps win on
+// cubes whatever the split: 65^3 13.7 / 13.3, 97^3 37 / 27.7.
+template <class St> bool stream3_pays(lbm_ctx* c) {
+    if (c->two_steps_pay < 0) c->two_steps_pay = c->geo.N >= 250000u || c->geo.N > 42000u * stream3_split<St>(c).cost;
+    return c->two_steps_pay == 1;
 }
 
 // k launches of the 3D two-step kernel, A -> B, advancing t by 2 k
@@ -846,12 +868,7 @@ template <class St> void stream3_launches(lbm_ctx* c, int64_t k) {
     a.c = make_coef<typename St::R>(c);
     a.tiles_x = (c->geo.nx + kT3OutX - 1) / kT3OutX;
     a.tiles_y = (c->geo.ny + kT3OutY - 1) / kT3OutY;
-    static const int resident = [] {
-        int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stream3_kernel<St>, kT3Threads, 0) != hipSuccess) n = 1;
-        return std::max(n, 1);
-    }();
-    const uint32_t segs = stream3_segments(c->geo.nz, a.tiles_x * a.tiles_y, c->cus, resident);
+    const uint32_t segs = stream3_split<St>(c).segs;
     a.seg_planes = (c->geo.nz + segs - 1) / segs;
     a.segs = (c->geo.nz + a.seg_planes - 1) / a.seg_planes;
     const uint32_t blocks = a.tiles_x * a.tiles_y * a.segs;
@@ -1079,7 +1096,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
         } else if constexpr (sizeof(typename St::R) == 4) {
             // 3D: two steps per launch through the LDS plane ring (FP64's
             // ring would not fit the LDS)
-            if (c->steps_per_launch == 2 && n >= 2 && streamable3(c) && (c->steps_set || stream3_pays(c))) {
+            if (c->steps_per_launch == 2 && n >= 2 && streamable3(c) && (c->steps_set || stream3_pays<St>(c))) {
                 stream3_launches<St>(c, n / 2);
                 n -= n / 2 * 2;
             }
