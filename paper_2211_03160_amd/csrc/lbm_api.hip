@@ -760,17 +760,17 @@ template <class St, int RX, int RY, int KT> int64_t tile2_run(lbm_ctx* c, int64_
     return 0;
 }
 
-// Largest grid the tile kernel steps by default.  Measured on square
-// cavities, us per step, tile / streaming kernel (its best segment length):
-// FP32 2049x1537 24.7 / 30.3, 3073^2 71.6 / 69.6, 4097^2 124.8 / 113.3; FP16
-// 22.1 / 28.3, 67.6 / 68.3, 119 / 112; BF16 20.4 / 30.5, 61.8 / 70.0, 108 /
-// 112, 8193^2 437 / 364; FP16-f+FP32-g 21.9 / 31.9, 69.7 / 74.1, 121 / 120.
-// FP64 8193^2 1096 / 1779: the streaming kernel holds two steps at most.
+// Largest grid the tile kernel steps by default.  us per step, tiles /
+// streaming: FP32 2049^2 34.2 / 39.2, 4000x1700 49.7 / 53.3, 2700^2 52.8 / 51.3,
+// 2999^2 65.4 / 59.2; FP16 2500^2 44.6 / 44.5, 2850^2 57.4 / 58.4, 2999^2 63.6 /
+// 59.0, 3500^2 84.5 / 76.2; BF16 2850^2 52.3 / 59.3, 2999^2 58.6 / 58.9, 3200^2
+// 65.9 / 61.9, 3800^2 89.4 / 82.0; FP16-f+FP32-g 2850^2 58.6 / 63.2, 2999^2 64.9 /
+// 62.8, 3400^2 81.3 / 72.5.  FP64 8193^2 1096 / 1779: the streaming kernel holds
+// two steps at most.
 template <class St> constexpr uint32_t tile2_most_nodes() {
     if (sizeof(typename St::R) == 8) return UINT32_MAX;
-    constexpr bool same = sizeof(typename St::TF) == sizeof(typename St::TG);
-    constexpr bool bf16 = std::is_same_v<typename St::EF, EB16>;
-    return bf16 || !same ? 15000000u : 9000000u;
+    if (sizeof(typename St::TF) == 4) return 7000000u;
+    return std::is_same_v<typename St::EF, EB16> ? 9500000u : 8500000u;
 }
 
 // steps per launch on 32 x 16 and on 32 x 32 regions
