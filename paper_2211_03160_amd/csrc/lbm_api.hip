@@ -777,8 +777,8 @@ template <class St> constexpr uint32_t tile2_most_nodes() {
 template <class St> constexpr int tile2_mid_steps() { return sizeof(typename St::R) == 8 ? 4 : 5; }
 template <class St> constexpr int tile2_big_steps() { return sizeof(typename St::TF) == 4 ? 5 : 4; }
 
-// n steps of a 2D cavity whose steps per launch were not set: through the
-// tile kernel where it is the fastest; returns the steps left over.
+// Steps of a 2D cavity whose steps per launch were not set go through the tile
+// kernel where it is the fastest; tile2_auto returns the steps left over.
 //
 // The region grows with the grid, which trades the latency of a launch (K
 // collisions of one wavefront per SIMD in a 16 x 16 region) for less halo
@@ -793,20 +793,32 @@ template <class St> constexpr int tile2_big_steps() { return sizeof(typename St:
 // five): each step spends 30 % of its instructions on the rounding.  Grids
 // lower than a tile's 24 output rows keep the streaming kernel, whose
 // segments fit any height, unless the launch is latency-bound anyway.
-template <class St> int64_t tile2_auto(lbm_ctx* c, int64_t n) {
+struct Tile2Choice {
+    int region;  // 0: 16 x 16, 1: 32 x 16, 2: 32 x 32
+    int steps;   // per launch; 0: not through tiles
+};
+template <class St> Tile2Choice tile2_choice(const lbm_ctx* c) {
     const uint32_t nx = c->geo.nx, ny = c->geo.ny;
-    if (c->geo.N > tile2_most_nodes<St>() || (ny < 24 && c->geo.N > 65536u)) return n;
+    if (c->geo.N > tile2_most_nodes<St>() || (ny < 24 && c->geo.N > 65536u)) return {0, 0};
     constexpr bool f64 = sizeof(typename St::R) == 8;
     constexpr int kMid = tile2_mid_steps<St>(), kBig = tile2_big_steps<St>();
     auto tiles = [&](uint32_t ox, uint32_t oy) { return (uint64_t)((nx + ox - 1) / ox) * ((ny + oy - 1) / oy); };
     const uint64_t cus = (uint64_t)std::max(c->cus, 1);
-    if (tiles(8, 8) <= 2 * cus) return tile2_run<St, 16, 16, 0>(c, n, 5);
-    if constexpr (f64) {
-        return tile2_run<St, 32, 16, kMid>(c, n, kMid);
-    } else {
-        if (tiles(24, 8) <= 4 * cus) return tile2_run<St, 32, 16, kMid>(c, n, kMid);
-        return tile2_run<St, 32, 32, kBig>(c, n, kBig);
-    }
+    if (tiles(8, 8) <= 2 * cus) return {0, 5};
+    // a launch holds less than 2^32 threads: FP64 grids of a few columns or
+    // rows can have more tiles of 512
+    if (tiles(32 - 2 * (kMid - 1), 16 - 2 * (kMid - 1)) * 512 > 0xff000000ull) return {0, 0};
+    if (f64 || tiles(24, 8) <= 4 * cus) return {1, kMid};
+    return {2, kBig};
+}
+
+template <class St> int64_t tile2_auto(lbm_ctx* c, int64_t n) {
+    const Tile2Choice t = tile2_choice<St>(c);
+    if (t.steps == 0) return n;
+    if (t.region == 0) return tile2_run<St, 16, 16, 0>(c, n, t.steps);
+    if (t.region == 1) return tile2_run<St, 32, 16, tile2_mid_steps<St>()>(c, n, t.steps);
+    if constexpr (sizeof(typename St::R) == 4) return tile2_run<St, 32, 32, tile2_big_steps<St>()>(c, n, t.steps);
+    return n;
 }
 
 // z segments of the 3D two-step kernel.  Each segment repeats the first
