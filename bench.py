@@ -36,10 +36,6 @@ METRIC = "GLUPS & %HBM peak, FP32 vs FP16-store, 8193² D2Q9+D2Q5 / 385³ D3Q19+
 KERNEL_SOURCES = ["paper_2211_03160_amd/csrc/kernels.hpp", "paper_2211_03160_amd/csrc/lattice.hpp",
                   "paper_2211_03160_amd/csrc/tile2d.hpp", "paper_2211_03160_amd/csrc/stream3d.hpp",
                   "paper_2211_03160_amd/csrc/lbm_api.hip"]
-# 2D with FP64 storage runs through LDS tiles, this many steps per launch,
-# until a count is set (the count that a context reports is the streaming
-# kernel's)
-TILE_STEPS_FP64 = 4
 TRAFFIC_FILES = {5: os.path.join(ROOT, "profiles", "stream5_d2q9_fp32_8193_counters.txt"),
                  1: os.path.join(ROOT, "profiles", "step_d2q9_fp32_8193_counters.txt")}
 TRAFFIC_FILES_3D = {2: os.path.join(ROOT, "profiles", "stream3d_d3q19_fp32_385_counters.txt"),
@@ -133,7 +129,7 @@ def run_case(cfg, warmup, steps, seed, noise, want_nu=True, steps_per_launch=Non
     cav.step(warmup)
     ms = timed_steps(cav, steps)
     out = {"ms_per_step": ms, "glups": cav.N / (ms * 1e-3) / 1e9,
-           "steps_per_launch": cav.steps_per_launch,
+           "steps_per_launch": cav.launch_steps,
            "bytes_per_update": cav.bytes_per_update()}
     out["hbm_gbs_algorithmic"] = out["glups"] * out["bytes_per_update"]
     if want_nu:
@@ -452,10 +448,7 @@ def main():
             "peak_tflops": PEAK_FP32_PACKED_TFLOPS, "frac": round(tflops / PEAK_FP32_PACKED_TFLOPS, 4),
             "peak_nonpacked_tflops": PEAK_FP32_TFLOPS, "frac_nonpacked": round(tflops / PEAK_FP32_TFLOPS, 4),
             "issue_frac": round(insts * 4 / 1024 / 2.4e9 / launch_s, 4) if insts else None}
-    ref64["bytes_per_update"] *= ref64["steps_per_launch"] / TILE_STEPS_FP64
-    ref64["steps_per_launch"] = TILE_STEPS_FP64
-    ref64["hbm_gbs_algorithmic"] = ref64["glups"] * ref64["bytes_per_update"]
-    ref64["roofline"] = hbm_roofline(ref64, N, f"lbm::tile2_kernel<StF64, 32, 16, {TILE_STEPS_FP64}>",
+    ref64["roofline"] = hbm_roofline(ref64, N, f"lbm::tile2_kernel<StF64, 32, 16, {ref64['steps_per_launch']}>",
                                      ceil["copy"]["gbs"])
 
     variants = {"rb2d_8193_fp64": {**ref64}}

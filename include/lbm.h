@@ -208,6 +208,14 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n);
 lbm_status lbm_set_steps_per_launch(lbm_ctx* c, int32_t steps);
 int32_t lbm_get_steps_per_launch(const lbm_ctx* c); /* 0 for NULL */
 
+/* Steps that a full launch of lbm_step advances now: the count that was set,
+ * or the one lbm_step chooses for the grid (1 for a batch member; 0 for
+ * NULL).  lbm_reset_steps_per_launch takes a count that was set back:
+ * lbm_step chooses again, as after lbm_create.  LBM_E_STATE for a batch
+ * member.                                                                */
+int32_t lbm_launch_steps(lbm_ctx* c);
+lbm_status lbm_reset_steps_per_launch(lbm_ctx* c);
+
 /* Debug mode (on = 1; off = 0, the default): before every kernel launch of
  * lbm_step, the population buffer the launch writes is filled with all-one
  * bits (NaN in every storage type; the padding beyond the last node stays

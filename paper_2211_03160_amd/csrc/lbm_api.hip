@@ -1156,6 +1156,31 @@ lbm_status lbm_set_steps_per_launch(lbm_ctx* c, int32_t steps) {
 
 int32_t lbm_get_steps_per_launch(const lbm_ctx* c) { return c ? c->steps_per_launch : 0; }
 
+int32_t lbm_launch_steps(lbm_ctx* c) {
+    if (!c) return 0;
+    int32_t k = 1;
+    (void)dispatch(c, [&](auto dimc, auto stc) -> lbm_status {
+        using St = decltype(stc);
+        if constexpr (decltype(dimc)::value == 2) {
+            const int32_t tiles = c->steps_set || c->view ? 0 : tile2_choice<St>(c).steps;
+            k = tiles ? tiles : streamable(c) ? c->steps_per_launch : 1;
+        } else if constexpr (sizeof(typename St::R) == 4) {
+            if (c->steps_per_launch == 2 && streamable3(c) && (c->steps_set || stream3_pays<St>(c))) k = 2;
+        }
+        return LBM_OK;
+    });
+    return k;
+}
+
+lbm_status lbm_reset_steps_per_launch(lbm_ctx* c) {
+    lbm_status st = enter(c);
+    if (st) return st;
+    if (c->view) return reject_view(c, "lbm_reset_steps_per_launch");
+    c->steps_per_launch = default_steps_per_launch(c->p.dim, c->p.storage);
+    c->steps_set = false;
+    return LBM_OK;
+}
+
 lbm_status lbm_set_debug_poison(lbm_ctx* c, int32_t on) {
     lbm_status st = enter(c);
     if (st) return st;

@@ -27,6 +27,7 @@ STATUS = {0: "LBM_OK", -1: "LBM_E_INVALID", -2: "LBM_E_DEVICE",
 EXPORTS = ["lbm_derive", "lbm_workspace_bytes", "lbm_bytes_per_update",
            "lbm_create", "lbm_init", "lbm_init_fields", "lbm_step",
            "lbm_set_steps_per_launch", "lbm_get_steps_per_launch",
+           "lbm_launch_steps", "lbm_reset_steps_per_launch",
            "lbm_set_debug_poison", "lbm_get_debug_poison",
            "lbm_fields", "lbm_nusselt", "lbm_wall_flux", "lbm_diagnostics",
            "lbm_state_bytes", "lbm_export_state", "lbm_import_state",
@@ -112,6 +113,9 @@ def lib():
         L.lbm_set_steps_per_launch.argtypes = [P, C.c_int32]
         L.lbm_get_steps_per_launch.argtypes = [P]
         L.lbm_get_steps_per_launch.restype = C.c_int32
+        L.lbm_launch_steps.argtypes = [P]
+        L.lbm_launch_steps.restype = C.c_int32
+        L.lbm_reset_steps_per_launch.argtypes = [P]
         L.lbm_set_debug_poison.argtypes = [P, C.c_int32]
         L.lbm_get_debug_poison.argtypes = [P]
         L.lbm_get_debug_poison.restype = C.c_int32
@@ -317,6 +321,16 @@ class Cavity:
     def steps_per_launch(self, k: int):
         self._check(lib().lbm_set_steps_per_launch(self._h, int(k)))
 
+    def reset_steps_per_launch(self):
+        """Back to the launches that step() chooses by itself."""
+        self._check(lib().lbm_reset_steps_per_launch(self._h))
+
+    @property
+    def launch_steps(self) -> int:
+        """Steps that a full launch of step() advances now: the count that was
+        set, or the one chosen for the grid."""
+        return int(lib().lbm_launch_steps(self._h))
+
     @property
     def debug_poison(self) -> bool:
         """Debug mode: the buffer each launch writes is filled with NaN
@@ -385,9 +399,9 @@ class Cavity:
         return derive(self.cfg)
 
     def bytes_per_update(self) -> float:
-        """Algorithmic HBM bytes per lattice update at the current number
-        of steps per launch."""
-        return bytes_per_update(self.cfg) / self.steps_per_launch
+        """Algorithmic HBM bytes per lattice update of the launches that
+        step() takes now."""
+        return bytes_per_update(self.cfg) / self.launch_steps
 
 
 class _View(Cavity):
