@@ -62,6 +62,7 @@ bool row_grid(int64_t n, int64_t h, int64_t w, int64_t c, RowShape* a, dim3* gri
 }
 
 constexpr size_t kMaxLds = 160 * 1024;
+constexpr uint32_t kMostBlocks = 65536;  // of kernels whose blocks loop over any number of pieces
 
 template <int WM, int WN, int MT, int NT> bool conv3x3_lds_go(ConvArgs a, uint32_t taps, hipStream_t s) {
     constexpr uint32_t BM = 16 * MT * WM, BN = 16 * NT * WN;
@@ -173,7 +174,7 @@ lbm_status lbm_nn_conv3x3_flip_many(int32_t count, const uint16_t* const* wt, co
             if (a.first[k] + blocks > 0x7fffffffull) return nn_fail(LBM_E_INVALID, "conv3x3_flip: layer too large");
             a.first[k + 1] = a.first[k] + (uint32_t)blocks;
         }
-        hipLaunchKernelGGL(wflip_kernel, dim3(a.first[a.count]), dim3(256), 0, (hipStream_t)stream, a);
+        hipLaunchKernelGGL(wflip_kernel, dim3(std::min(a.first[a.count], kMostBlocks)), dim3(256), 0, (hipStream_t)stream, a);
         const lbm_status st = launched("conv3x3_flip");
         if (st) return st;
     }
@@ -247,8 +248,9 @@ lbm_status lbm_nn_conv3x3_wgrad(const uint16_t* x, const uint16_t* dz, int32_t n
     lbm_status st = launched("conv3x3_wgrad");
     if (st) return st;
     const bool sum_bias = db && a.chunks > 1;
-    const SumChunksArgs sa{partial, dw, (uint32_t)count, a.chunks, a.bias, db, sum_bias ? (uint32_t)cout : 0u};
-    const unsigned grid = (unsigned)((count + 63) / 64 + (sum_bias ? (cout + 63) / 64 : 0));
+    const SumChunksArgs sa{partial, dw, count, a.chunks, a.bias, db, sum_bias ? (uint32_t)cout : 0u};
+    const size_t blocks = (count + 63) / 64 + (sum_bias ? (cout + 63) / 64 : 0);
+    const unsigned grid = (unsigned)std::min<size_t>(blocks, kMostBlocks);
     hipLaunchKernelGGL(sum_chunks_kernel, dim3(grid), dim3(256), 0, s, sa);
     return launched("conv3x3_wgrad sum");
 }

@@ -353,21 +353,24 @@ struct FlipArgs {
 };
 __global__ __launch_bounds__(256) void wflip_kernel(FlipArgs a) {
     __shared__ uint16_t t[32][33];
-    int l = 0;
-    while (l + 1 < a.count && blockIdx.x >= a.first[l + 1]) ++l;
-    const uint32_t ci = (uint32_t)a.cin[l], co = (uint32_t)a.cout[l];
-    const uint32_t ti = (ci + 31) / 32, to = (co + 31) / 32, r = blockIdx.x - a.first[l];
-    const uint32_t tap = r / (ti * to), i0 = r % ti * 32, o0 = r / ti % to * 32;
     const uint32_t x = threadIdx.x & 31, y = threadIdx.x >> 5;
-    const uint16_t* src = a.wt[l] + (size_t)(8 - tap) * co * ci;
-    uint16_t* dst = a.wf[l] + (size_t)tap * co * ci;
+    int l = 0;
+    for (uint32_t b = blockIdx.x; b < a.first[a.count]; b += gridDim.x) {
+        while (l + 1 < a.count && b >= a.first[l + 1]) ++l;
+        const uint32_t ci = (uint32_t)a.cin[l], co = (uint32_t)a.cout[l];
+        const uint32_t ti = (ci + 31) / 32, to = (co + 31) / 32, r = b - a.first[l];
+        const uint32_t tap = r / (ti * to), i0 = r % ti * 32, o0 = r / ti % to * 32;
+        const uint16_t* src = a.wt[l] + (size_t)(8 - tap) * co * ci;
+        uint16_t* dst = a.wf[l] + (size_t)tap * co * ci;
+        if (b > blockIdx.x) __syncthreads();  // the previous square has been read
 #pragma unroll
-    for (uint32_t k = 0; k < 32; k += 8)
-        if (o0 + y + k < co && i0 + x < ci) t[y + k][x] = src[(size_t)(o0 + y + k) * ci + i0 + x];
-    __syncthreads();
+        for (uint32_t k = 0; k < 32; k += 8)
+            if (o0 + y + k < co && i0 + x < ci) t[y + k][x] = src[(size_t)(o0 + y + k) * ci + i0 + x];
+        __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < 32; k += 8)
-        if (i0 + y + k < ci && o0 + x < co) dst[(size_t)(i0 + y + k) * co + o0 + x] = t[x][y + k];
+        for (uint32_t k = 0; k < 32; k += 8)
+            if (i0 + y + k < ci && o0 + x < co) dst[(size_t)(i0 + y + k) * co + o0 + x] = t[x][y + k];
+    }
 }
 
 // division of e < 2^31 by d (Granlund and Montgomery, 1994): with s = ceil(log2
@@ -640,34 +643,39 @@ void wgrad_kernel(WGradArgs a) {
 struct SumChunksArgs {
     const float* partial;
     float* dw;
-    uint32_t count, chunks;
+    size_t count;
+    uint32_t chunks;
     const float* bias;
     float* db;
     uint32_t bias_count;
 };
 __global__ __launch_bounds__(256) void sum_chunks_kernel(SumChunksArgs a) {
     __shared__ v4f lds[256];
-    const uint32_t col = threadIdx.x & 15, part = threadIdx.x >> 4, blocks_w = (a.count + 63) / 64;
-    const bool w = blockIdx.x < blocks_w;
-    const float* src = w ? a.partial : a.bias;
-    float* dst = w ? a.dw : a.db;
-    const uint32_t count = w ? a.count : a.bias_count;
-    const uint32_t e = (blockIdx.x - (w ? 0 : blocks_w)) * 64 + col * 4;  // counts are multiples of 16
-    v4f s = v4f{0.f, 0.f, 0.f, 0.f};
-    if (e < count)
-        for (uint32_t c = part; c < a.chunks; c += 16) {
-            const float* p = src + (size_t)c * count + e;
+    const uint32_t col = threadIdx.x & 15, part = threadIdx.x >> 4;
+    const size_t blocks_w = (a.count + 63) / 64, blocks = blocks_w + (a.bias_count + 63) / 64;
+    for (size_t b = blockIdx.x; b < blocks; b += gridDim.x) {
+        const bool w = b < blocks_w;
+        const float* src = w ? a.partial : a.bias;
+        float* dst = w ? a.dw : a.db;
+        const size_t count = w ? a.count : a.bias_count;
+        const size_t e = (b - (w ? 0 : blocks_w)) * 64 + col * 4;  // counts are multiples of 16
+        v4f s = v4f{0.f, 0.f, 0.f, 0.f};
+        if (e < count)
+            for (uint32_t c = part; c < a.chunks; c += 16) {
+                const float* p = src + c * count + e;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] += p[j];
+                for (int j = 0; j < 4; ++j) s[j] += p[j];
+            }
+        if (b > blockIdx.x) __syncthreads();  // the previous sums have been read
+        lds[threadIdx.x] = s;
+        for (uint32_t o = 128; o >= 16; o >>= 1) {
+            __syncthreads();
+            if (threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
         }
-    lds[threadIdx.x] = s;
-    for (uint32_t o = 128; o >= 16; o >>= 1) {
-        __syncthreads();
-        if (threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
-    }
-    if (part == 0 && e < count) {
+        if (part == 0 && e < count) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) dst[e + j] = lds[threadIdx.x][j];
+            for (int j = 0; j < 4; ++j) dst[e + j] = lds[threadIdx.x][j];
+        }
     }
 }
 

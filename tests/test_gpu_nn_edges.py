@@ -125,3 +125,28 @@ def test_wgrad_of_many_small_images(n, h, w, ci, co):
         got, bias = _wgrad(_dev_bf16(x), _dev_bf16(dz), co, chunks)
         assert np.all(np.abs(got - ref) <= 1e-5 * scale + 1e-6)
         assert np.all(np.abs(bias - bref) <= 1e-5 * bscale + 1e-6)
+
+
+def test_more_weights_than_a_launch_holds_blocks_for():
+    """Flips and chunk sums whose pieces exceed 65536 blocks, each block then
+    taking several: exact against torch (one pixel, whose products and sums are
+    exact in FP32 with these values)."""
+    import torch
+    from paper_2211_03160_amd import nn
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    val = lambda *s: torch.randint(-8, 9, s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    raw = lambda t: t.contiguous().view(torch.int16)  # noqa: E731
+    ci, co = 2752, 2784  # 9 x 86 x 87 squares of 32 x 32
+    layers = [(raw(val(9, o, i)), i, o) for i, o in ((16, 32), (ci, co), (48, 16))]
+    for (w, i, o), wf in zip(layers, nn.conv3x3_flip_many(layers)):
+        assert torch.equal(wf, w.flip(0).transpose(1, 2).contiguous())
+    x, dz = val(3, 1, 1, ci), val(3, 1, 1, 256)
+    n = 9 * 256 * ci  # 99072 blocks of 64 sums
+    partial = torch.full((2 * n,), float("nan"), device="cuda")
+    dw, db = torch.full((9, 256, ci), float("nan"), device="cuda"), torch.full((256,), float("nan"), device="cuda")
+    nn._check(nn.lib().lbm_nn_conv3x3_wgrad(nn._p(raw(x)), nn._p(raw(dz)), 3, 1, 1, ci, 256, nn._p(partial), 2,
+                                            nn._p(dw), nn._p(db), nn._s()))
+    want = torch.zeros(9, 256, ci, device="cuda")
+    want[4] = dz.float().reshape(3, 256).t().contiguous() @ x.float().reshape(3, ci)
+    assert torch.equal(dw, want) and torch.equal(db, dz.float().sum((0, 1, 2)))
