@@ -627,7 +627,7 @@ bool streamable3(const lbm_ctx* c) {
 // resident wavefront the time goes as (A / r + 1/2) (r + NS - 1), least at
 // r = sqrt(2 (NS - 1) A).  FP32 at five steps (kept in step, so that long
 // segments do not cost memory traffic) follows that; GLUPS at 24 / 32 / 40 /
-// 56 / 72 rows: 4097^2 (rule 35) 150 / 149 / 152 / 145 / 158, 6145x5000 (47)
+// 56 / 72 rows: 4097^2 (rule 35: 164) 150 / 149 / 152 / 145 / 158, 6145x5000 (47)
 // 164 / 168 / 172 / 170 / 168, 12000x6000 (72) 168 / 174 / 180 / 182 / 182,
 // 8193^2 (70) 168 / 172 / 179 / 178 / 180.
 // 16-bit storage at three and four steps follows it from 16 rows on, times a
@@ -792,7 +792,8 @@ template <class St> constexpr int tile2_big_steps() { return sizeof(typename St:
 // runs four steps on 32 x 32 regions (FP16 2049x1537 22.1 against 23.6 with
 // five): each step spends 30 % of its instructions on the rounding.  Grids
 // lower than a tile's 24 output rows keep the streaming kernel, whose
-// segments fit any height, unless the launch is latency-bound anyway.
+// segments fit any height, unless the launch is latency-bound anyway (whether
+// 32 x 16 regions, which store 8 or 10 rows, would be faster is not measured).
 struct Tile2Choice {
     int region;  // 0: 16 x 16, 1: 32 x 16, 2: 32 x 32
     int steps;   // per launch; 0: not through tiles

@@ -9,16 +9,14 @@
 // - 1)) nodes.  Every node update is step_node on the same (storage-rounded)
 // values as a one-step launch, so results are bitwise those of single steps.
 //
-// The register-row kernel (stream_kernel) walks a wavefront down at least 8
-// rows plus 3 NS rows of pipeline fill, a serial chain of 60 to 100 us, and
+// The register-row kernel (stream_kernel) walks a wavefront down the rows of a
+// segment plus 3 NS rows of pipeline fill, a serial chain of 60 to 100 us, and
 // leaves most of the chip idle below about 2000 units.  Here a launch is K
 // collisions deep whatever the grid, and a wavefront holds no rings: 56
 // registers in FP32, so 8 wavefronts per SIMD cover the barriers.
 #pragma once
 
 namespace lbm {
-
-constexpr int kTile2MaxSteps = 6;
 
 template <class St> struct Tile2Args {
     const typename St::TF* fsrc;
@@ -28,7 +26,7 @@ template <class St> struct Tile2Args {
     double* flux;       // wall heat flux area: two slots, faces back to back
     uint32_t slot[2];   // first element of flux slot 0 and slot 1
     int32_t t_parity;   // (t of the input state) mod 2: step j writes slot (t + j) mod 2
-    int32_t steps;      // K, 2 .. kTile2MaxSteps
+    int32_t steps;      // K, 2 .. 5
     uint32_t tiles_x, tiles;
     uint32_t blocks_per_xcd;
     Geometry geo;
