@@ -187,7 +187,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n);
  * fastest for its storage on a large grid: in 2D 5 (FP32), 4 (FP16-f+FP32-g,
  * BF16), 3 (FP16), 2 (FP64); in 3D 2 (FP32) and 1 (the others).  Until a
  * count is set, lbm_step takes other launches where the grid's size makes
- * them faster (2D: 4 or 5 steps through LDS tiles on grids below 7 to 9.5
+ * them faster (2D: 4 or 5 steps through LDS tiles on grids below 8.7 to 10.5
  * million nodes, with FP64 storage on all grids; 3D with FP32 storage: one
  * step on most grids below 250 thousand nodes); lbm_get_steps_per_launch keeps
  * returning the large-grid count.  A count that was set is taken

@@ -760,17 +760,19 @@ template <class St, int RX, int RY, int KT> int64_t tile2_run(lbm_ctx* c, int64_
     return 0;
 }
 
-// Largest grid the tile kernel steps by default.  us per step, tiles /
-// streaming: FP32 2049^2 34.2 / 39.2, 4000x1700 49.7 / 53.3, 2700^2 52.8 / 51.3,
-// 2999^2 65.4 / 59.2; FP16 2500^2 44.6 / 44.5, 2850^2 57.4 / 58.4, 2999^2 63.6 /
-// 59.0, 3500^2 84.5 / 76.2; BF16 2850^2 52.3 / 59.3, 2999^2 58.6 / 58.9, 3200^2
-// 65.9 / 61.9, 3800^2 89.4 / 82.0; FP16-f+FP32-g 2850^2 58.6 / 63.2, 2999^2 64.9 /
-// 62.8, 3400^2 81.3 / 72.5.  FP64 8193^2 1096 / 1779: the streaming kernel holds
-// two steps at most.
+// Largest grid the tile kernel steps by default: from there on streaming is no
+// slower on any shape measured (below, it is between 10 % slower and 10 %
+// faster, by how its segments fill the chip).  us per step, tiles / streaming:
+// FP32 2650x2700 53.3 / 59.3, 2000x3700 54.2 / 58.6, 2850x2950 61.4 / 55.7,
+// 2100x4097 (8.6 M) 62.6 / 63.9, 2999^2 65.4 / 59.2, 4097x2200 66.6 / 60.4; FP16
+// 2100x4097 60.3 / 65.0, 2999^2 63.6 / 59.0, 3500^2 84.5 / 76.2; BF16 2100x4097
+// 55.3 / 62.7, 2999^2 58.6 / 58.9, 4097x2500 (10.2 M) 65.2 / 66.8, 3400^2 72.8 /
+// 68.2; FP16-f+FP32-g 2100x4097 61.5 / 66.0, 2999^2 64.9 / 62.8, 3400^2 81.3 /
+// 72.5.  FP64 8193^2 1096 / 1779: the streaming kernel holds two steps at most.
 template <class St> constexpr uint32_t tile2_most_nodes() {
     if (sizeof(typename St::R) == 8) return UINT32_MAX;
-    if (sizeof(typename St::TF) == 4) return 7000000u;
-    return std::is_same_v<typename St::EF, EB16> ? 9500000u : 8500000u;
+    if (sizeof(typename St::TF) == 4) return 8700000u;
+    return std::is_same_v<typename St::EF, EB16> ? 10500000u : 8800000u;
 }
 
 // steps per launch on 32 x 16 and on 32 x 32 regions
