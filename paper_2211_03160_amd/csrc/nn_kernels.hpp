@@ -415,8 +415,8 @@ struct WGradArgs {
 //
 // The kernel this replaced ran one tap per wavefront: it loaded both operands
 // nine times and transposed them through 16-bit LDS writes.  us before /
-// after, sums included: 32 -> 32 channels at 16 x 136 x 136 156 / 31, 96 -> 32
-// 202 / 42, 64 -> 64 at 68 x 68 96 / 27, 256 -> 256 at 17 x 17 103 / 34.  Bound
+// after, sums included: 32 -> 32 channels at 16 x 136 x 136 156 / 28, 96 -> 32
+// 202 / 45, 64 -> 64 at 68 x 68 96 / 26, 256 -> 256 at 17 x 17 103 / 33.  Bound
 // by the latency of a tile's loads and the partial sums' traffic: two
 // wavefronts per SIMD (the accumulators) hold few tiles in flight.
 // LDS pixels carry 32 bytes of padding, so four consecutive pixels of a
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(256) void sum_chunks_kernel(SumChunksArgs a) {
 // element-per-thread kernels (below) spend their time on four 64-bit
 // divisions per value.  In one gradient of the 257^2
 // network (batch 16) the upsampling, concatenation, pooling and ReLU passes,
-// forward and backward, took 670 us in 41 launches; joined they take 115 us in
+// forward and backward, took 670 us in 41 launches; joined they take 104 us in
 // 12, and the ReLU masks of the others ride in the convolutions' stores.
 struct Vec8 {
     v4u v;
