@@ -231,6 +231,7 @@ lbm_status lbm_nn_conv3x3_wgrad(const uint16_t* x, const uint16_t* dz, int32_t n
         a.per = (a.tiles + want - 1) / want;
         a.chunks = (a.tiles + a.per - 1) / a.per;
         a.bias = !db ? nullptr : a.chunks == 1 ? db : partial + (size_t)(chunks - 1) * count;
+        a.partial = a.chunks == 1 ? dw : partial;  // one chunk: its sums are the result
         const uint32_t blocks = a.chunks * (uint32_t)((cout + 32 * WCO - 1) / (32 * WCO)) *
                                 (uint32_t)((cin + 32 * WCI - 1) / (32 * WCI));
         const dim3 grid((blocks + 7) / 8 * 8);
@@ -247,11 +248,13 @@ lbm_status lbm_nn_conv3x3_wgrad(const uint16_t* x, const uint16_t* dz, int32_t n
     else go(I1{}, I1{}, I4{}, I2{});
     lbm_status st = launched("conv3x3_wgrad");
     if (st) return st;
-    const bool sum_bias = db && a.chunks > 1;
-    const SumChunksArgs sa{partial, dw, count, a.chunks, a.bias, db, sum_bias ? (uint32_t)cout : 0u};
-    const size_t blocks = (count + 63) / 64 + (sum_bias ? (cout + 63) / 64 : 0);
-    const unsigned grid = (unsigned)std::min<size_t>(blocks, kMostBlocks);
-    hipLaunchKernelGGL(sum_chunks_kernel, dim3(grid), dim3(256), 0, s, sa);
+    if (a.chunks == 1) return LBM_OK;
+    const SumChunksArgs sa{partial, dw, count, a.chunks, a.bias, db, db ? (uint32_t)cout : 0u};
+    const bool few = a.chunks <= 4;
+    const size_t each = few ? 1024 : 64, blocks = (count + each - 1) / each + (sa.bias_count + each - 1) / each;
+    const dim3 grid((unsigned)std::min<size_t>(blocks, kMostBlocks));
+    if (few) hipLaunchKernelGGL(sum_chunks_kernel<1>, grid, dim3(256), 0, s, sa);
+    else hipLaunchKernelGGL(sum_chunks_kernel<16>, grid, dim3(256), 0, s, sa);
     return launched("conv3x3_wgrad sum");
 }
 

@@ -639,12 +639,14 @@ void wgrad_kernel(WGradArgs a) {
 }
 
 // dw[e] = sum over the chunks of partial[c][e], and db likewise: a block takes
-// 64 values, its 16 rows of threads every 16th chunk, and the row sums are
-// added in a fixed tree; the bias gradient's in FP64, as the matrix cores' sums
-// of a chunk lose by themselves what its former kernels lost in all (relative
-// error at 16 x 136 x 136, 32 channels: 7.8e-8 before, 9.4e-8 with FP32 sums
-// here, 3.6e-8 so; the weights' is below the former one either way, 3.7e-7 and
-// 1.2e-7)
+// 64 values, its 16 rows of threads every 16th chunk, and the row sums are added
+// in a fixed tree; with four chunks or fewer a block takes 1024 values, a
+// thread's in order (512 -> 512 channels at 1 x 16 x 16, weight gradient and
+// sums: 38 us with rows of which two held chunks, 20).  The bias gradient's sums
+// are FP64, as the matrix cores' sums of a chunk lose by themselves what its
+// former kernels lost in all (relative error at 16 x 136 x 136, 32 channels:
+// 7.8e-8 before, 9.4e-8 with FP32 sums here, 3.6e-8 so; the weights' is below the
+// former one either way, 3.7e-7 and 1.2e-7).
 struct SumChunksArgs {
     const float* partial;
     float* dw;
@@ -654,23 +656,26 @@ struct SumChunksArgs {
     float* db;
     uint32_t bias_count;
 };
+template <uint32_t ROWS>  // of threads: 16, or 1
 __global__ __launch_bounds__(256) void sum_chunks_kernel(SumChunksArgs a) {
     __shared__ v4d lds[256];
-    const uint32_t col = threadIdx.x & 15, part = threadIdx.x >> 4;
-    const size_t blocks_w = (a.count + 63) / 64, blocks = blocks_w + (a.bias_count + 63) / 64;
+    constexpr uint32_t cols = 256 / ROWS, each = cols * 4;
+    const uint32_t col = threadIdx.x % cols, part = threadIdx.x / cols;
+    const size_t blocks_w = (a.count + each - 1) / each;
+    const size_t blocks = blocks_w + (a.bias_count + each - 1) / each;
     // block b of the sums, in the precision of vector v
     auto sum = [&](auto v, const float* src, float* dst, size_t count, size_t b) __attribute__((always_inline)) {
         using V = decltype(v);
         V* mine = (V*)lds;
-        const size_t e = b * 64 + col * 4;  // counts are multiples of 16
+        const size_t e = b * each + col * 4;  // counts are multiples of 16
         if (e < count)
-            for (uint32_t c = part; c < a.chunks; c += 16) {
+            for (uint32_t c = part; c < a.chunks; c += ROWS) {
                 const float* p = src + c * count + e;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) v[j] += p[j];
             }
         mine[threadIdx.x] = v;
-        for (uint32_t o = 128; o >= 16; o >>= 1) {
+        for (uint32_t o = 128; o >= cols; o >>= 1) {
             __syncthreads();
             if (threadIdx.x < o) mine[threadIdx.x] += mine[threadIdx.x + o];
         }

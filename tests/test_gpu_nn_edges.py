@@ -121,7 +121,7 @@ def test_wgrad_of_many_small_images(n, h, w, ci, co):
     zero = np.zeros((3, 3, ci, co))
     _, ref, bref = R.conv3x3_backward(x, zero, dz)
     _, scale, bscale = R.conv3x3_backward(np.abs(x), zero, np.abs(dz))
-    for chunks in (1, 4, 50):
+    for chunks in (1, 2, 3, 5, 6, 50):
         got, bias = _wgrad(_dev_bf16(x), _dev_bf16(dz), co, chunks)
         assert np.all(np.abs(got - ref) <= 1e-5 * scale + 1e-6)
         assert np.all(np.abs(bias - bref) <= 1e-5 * bscale + 1e-6)
@@ -141,15 +141,18 @@ def test_more_weights_than_a_launch_holds_blocks_for():
     layers = [(raw(val(9, o, i)), i, o) for i, o in ((16, 32), (ci, co), (48, 16))]
     for (w, i, o), wf in zip(layers, nn.conv3x3_flip_many(layers)):
         assert torch.equal(wf, w.flip(0).transpose(1, 2).contiguous())
-    x, dz = val(3, 1, 1, ci), val(3, 1, 1, 256)
     n = 9 * 256 * ci  # 99072 blocks of 64 sums
-    partial = torch.full((2 * n,), float("nan"), device="cuda")
-    dw, db = torch.full((9, 256, ci), float("nan"), device="cuda"), torch.full((256,), float("nan"), device="cuda")
-    nn._check(nn.lib().lbm_nn_conv3x3_wgrad(nn._p(raw(x)), nn._p(raw(dz)), 3, 1, 1, ci, 256, nn._p(partial), 2,
-                                            nn._p(dw), nn._p(db), nn._s()))
-    want = torch.zeros(9, 256, ci, device="cuda")
-    want[4] = dz.float().reshape(3, 256).t().contiguous() @ x.float().reshape(3, ci)
-    assert torch.equal(dw, want) and torch.equal(db, dz.float().sum((0, 1, 2)))
+    for m, chunks in ((3, 2), (16 * 5, 7)):  # one chunk, and six: images of 16 x 1 pixels fill a tile each
+        x, dz = val(m, 16, 1, ci), val(m, 16, 1, 256)
+        x[:, 1:] = 0  # of which one holds values
+        dz[:, 1:] = 0
+        partial = torch.full((chunks * n,), float("nan"), device="cuda")
+        dw, db = torch.full((9, 256, ci), float("nan"), device="cuda"), torch.full((256,), float("nan"), device="cuda")
+        nn._check(nn.lib().lbm_nn_conv3x3_wgrad(nn._p(raw(x)), nn._p(raw(dz)), m, 16, 1, ci, 256, nn._p(partial), chunks,
+                                                nn._p(dw), nn._p(db), nn._s()))
+        want = torch.zeros(9, 256, ci, device="cuda")
+        want[4] = dz[:, 0, 0].float().t().contiguous() @ x[:, 0, 0].float()
+        assert torch.equal(dw, want) and torch.equal(db, dz.float().sum((0, 1, 2)))
 
 
 def test_bias_gradient_keeps_its_precision():
