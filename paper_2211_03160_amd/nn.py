@@ -115,8 +115,9 @@ def conv3x3_wgrad(x, dz, cout, dw, db):
     # with 16 / 48 / 64
     tiles = -(-cout // (64 if cout >= 64 else 32)) * -(-cin // (64 if cin >= 64 else 32))
     chunks = max(48, min(256, 384 // tiles))
-    # of 8 x 16 pixels, which low images may fill to a sixth and less: three a chunk
-    # (1 x 1 x 136, 288 -> 96: 29 us with its 17 in two chunks, 17 so)
+    # the kernel's pixel tiles are 8 x 16, which low images may fill to a sixth
+    # and less: at most three of them a chunk (1 x 1 x 136, 288 -> 96: 29 us with
+    # its 17 in two chunks, 17 so)
     pixel_tiles = -(-w // 8) * min(n * -(-h // 16), -(-n * (h + 1) // 16))
     chunks = int(max(1, min(chunks, max(n * h * w // 64, pixel_tiles // 3), (1 << 26) // (9 * cout * cin))))
     partial = torch.empty(chunks * 9 * cout * cin, dtype=torch.float32, device="cuda")
