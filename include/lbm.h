@@ -419,7 +419,8 @@ lbm_status lbm_batch_unstable(lbm_batch* b, int32_t* flags);
  * without an entry in ms_per_step, and are used from then on if they are
  * faster than every candidate: `best` then has tiles = 1 beside the fastest
  * candidate's shape, and a configuration that is given back with
- * lbm_batch_set_config keeps the launches it stands for.  The timing steps are real steps: t advances by
+ * lbm_batch_set_config keeps the launches it stands for.  The timing steps
+ * are real steps: t advances by
  * (steps + 1) x the steps per launch of every candidate.  ms_per_step
  * (nullable) receives up to LBM_BATCH_TUNE_MAX timings in candidate order,
  * ncand their number.                                                   */

@@ -58,7 +58,8 @@ lbm_status lbm_nn_conv3x3_masked(const uint16_t* x, int32_t n, int32_t h, int32_
  * db may be NULL; with db, cout <= 256).  `partial` is scratch of
  * chunks * 9 * cout * cin floats; pixels are split into at most `chunks`
  * ranges whose sums are added in a fixed order, so the result does not
- * depend on scheduling.                                                  */
+ * depend on scheduling.  n (h + 1) below 2^32 - 16, h below 2^30 - 256 (else
+ * LBM_E_INVALID).                                                        */
 lbm_status lbm_nn_conv3x3_wgrad(const uint16_t* x, const uint16_t* dz, int32_t n, int32_t h,
                                 int32_t w, int32_t cin, int32_t cout, float* partial,
                                 int32_t chunks, float* dw, float* db, void* stream);
